@@ -291,7 +291,7 @@ pr2_status pr2_moe_rollout_forward(const pr2_moe_desc* desc, const void* x, cons
  * FMA passes over x and the [T, N] logit gradient) and k > 64 returns PR2_ERR_UNSUPPORTED.
  * The pre-activations
  * are recomputed (nothing is saved from the forward call); on the bf16 MFMA path
- * (d % 256 == 0, m % 256 == 0) a, u, their gradients, g H and the per-route input gradients
+ * (d % 256 == 0, m % 128 == 0) a, u, their gradients, g H and the per-route input gradients
  * are held in bf16, with fp32 accumulation everywhere.
  */
 pr2_status pr2_moe_replay_backward(const pr2_moe_desc* desc, const void* x, const void* idx,

@@ -166,7 +166,7 @@ bwd_gemm(BwdArgs g) {
         // starts workgroups in index order), so the busiest experts neither pile
         // up on one XCD nor start last.
         const int nrt = MODE == WD ? g.d / BM : 2 * g.m / BM;
-        nct = MODE == WD ? g.m / BN : g.d / BN;
+        nct = MODE == WD ? (g.m + BN - 1) / BN : g.d / BN;
         const int per_e = nrt * nct;
         const int xcd = blockIdx.x % kNumXcd;
         const int local = blockIdx.x / kNumXcd;
@@ -186,7 +186,11 @@ bwd_gemm(BwdArgs g) {
     const int wr = wave >> 1;            // 64-row block of the output tile
     const int wc = wave & 1;             // 128-column block
     const int half = wave >> 2;          // operand this wavefront loads: 0 rows, 1 columns
-    const bool active = wr * WM < rows;
+    // DH and WD have m columns, a multiple of 128: the last panel may hold 128.
+    // Its copies then read its 128 columns twice (nothing is read past a row's
+    // end) and the wavefronts of its upper half only help copy.
+    const int ncols = MODE == DH ? min(BN, g.m - pn * BN) : MODE == WD ? min(BN, g.m - ct * BN) : BN;
+    const bool active = wr * WM < rows && wc * WN < ncols;
 
     // ---- operand loading.  Both operands are copied global -> LDS with
     // 16-byte direct-to-LDS loads; wavefronts 0-3 copy the row operand (C
@@ -227,7 +231,9 @@ bwd_gemm(BwdArgs g) {
     // a copy are the same for the whole wavefront, so their addresses are
     // formed on the scalar unit and each lane only adds its own offset.
     const int hi = lane >> 5;
-    const int cpat[2] = {8 * ((lane & 31) ^ (4 * hi)), 8 * ((lane & 31) ^ (4 * (hi + 2)))};
+    const int cmask = half == 1 && ncols < BN ? WN - 1 : BN - 1;
+    const int cpat[2] = {(8 * ((lane & 31) ^ (4 * hi))) & cmask,
+                         (8 * ((lane & 31) ^ (4 * (hi + 2)))) & cmask};
     constexpr bool kHasGather = (MODE == WD || MODE == WGU);
     const bool gathered = (MODE == WD && half == 0) || (MODE == WGU && half == 1);
     // plain strided operand: K row 0 at this tile's columns, row stride ld
@@ -1234,11 +1240,15 @@ hipError_t launch_generic_gemms(const pr2_moe_desc& d, const void* x, const void
 
 }  // namespace
 
+// The MFMA backward takes every width the MFMA forward takes (m % 128 == 0): an
+// odd multiple of 128 ends DH and WD in a half panel, whose wasted copies cost
+// far less than the one-thread-per-output kernels (a training pass of 1021
+// tokens, d 2048, 64 experts, k 6, m 1408: 475 ms with those, 1.43 ms here).
 bool bwd_mfma_ok(const pr2_moe_desc& d) {
     const int64_t lim = (int64_t)1 << 31;
     const int64_t Tk = d.T * (int64_t)d.k;
     // (route entries below 2^32 / k keep the multiply-high token division exact)
-    return mfma_shape_ok(d) && d.m % BN == 0 && d.d % BN == 0 && Tk * 2 * d.m < lim &&
+    return mfma_shape_ok(d) && d.m % WN == 0 && d.d % BN == 0 && Tk * 2 * d.m < lim &&
            Tk * (int64_t)d.k < ((int64_t)1 << 32);
 }
 
@@ -1299,7 +1309,7 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
 
     // gate gradient partials and the SwiGLU backward
     if (mfma) {
-        g.ntn = d.m / BN;
+        g.ntn = (d.m + BN - 1) / BN;
         LaunchScope scope("bwd_dh_swiglu", s);
         hipLaunchKernelGGL(bwd_gemm<DH>, grid_for(w.max_tiles * g.ntn), dim3(kThreads), 0, s, g);
     } else {
@@ -1455,7 +1465,8 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
         {
             LaunchScope scope("bwd_wgrad_down", s);
             hipLaunchKernelGGL(bwd_gemm<WD>,
-                               dim3((unsigned)(kNumXcd * experts_per_xcd * (d.d / BM) * (d.m / BN))),
+                               dim3((unsigned)(kNumXcd * experts_per_xcd * (d.d / BM) *
+                                               ((d.m + BN - 1) / BN))),
                                dim3(kThreads), 0, s, g);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
