@@ -31,7 +31,6 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short v4s __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) v4s lds_v4s;
 
 constexpr int BM = 256;         // output tile rows
@@ -82,28 +81,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     static_assert(n >= 0 && n < 16, "vmcnt field");
     __builtin_amdgcn_s_waitcnt(0x0f70 | n);
 }
-
-// Direct global -> LDS copy of 16 bytes per lane: lane l fills dst + 16 l
-// (dst is the same for the whole wavefront).  Written as inline assembly:
-// issued through the compiler builtin, every later LDS read that carries no
-// type-based alias information (the transposing reads do not) is made to wait
-// for all copies in flight, which serialises each K slice's copies with the
-// slice before.  The K loop waits for its own copies explicitly (vmcnt 0 ahead
-// of the barrier that publishes a stage), so nothing relies on that wait.
-// M0 takes the LDS base; the nop covers the M0-write -> LDS-DMA hazard.  The
-// compiler keeps no value of its own in M0 in these kernels (it sets M0 only
-// right before its own LDS-DMA and message instructions, and they use none),
-// so the clobber it warns about is harmless here.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(const void* src, const unsigned char* dst) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const lds_void*)dst);
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(src), "s"(m0)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
 
 // value of lane (l + n) mod 16 of this lane's group of 16 (DPP row rotate)
 template <int n>

@@ -42,6 +42,40 @@ __device__ __forceinline__ int load_id(const void* idx, int idx_dtype, int64_t p
     return idx_dtype == PR2_I16 ? (int)((const int16_t*)idx)[pos] : ((const int32_t*)idx)[pos];
 }
 
+// ----------------------------------------------------- copies into LDS ----
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Direct global -> LDS copy of 16 bytes per lane: lane l fills dst + 16 l
+// (dst is the same for the whole wavefront).  Written as inline assembly:
+// issued through the compiler builtin, every later LDS read that carries no
+// type-based alias information (the transposing reads do not) is made to wait
+// for all copies in flight, which serialises each K slice's copies with the
+// slice before.  The K loop waits for its own copies explicitly (vmcnt 0 ahead
+// of the barrier that publishes a stage), so nothing relies on that wait.
+// M0 takes the LDS base; the nop covers the M0-write -> LDS-DMA hazard.  The
+// compiler keeps no value of its own in M0 in these kernels (it sets M0 only
+// right before its own LDS-DMA and message instructions, and they use none),
+// so the clobber it warns about is harmless here.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void dma16(const void* src, const unsigned char* dst) {
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const lds_void*)dst);
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %0, off"
+                 :
+                 : "v"(src), "s"(m0)
+                 : "memory", "m0");
+}
+// The same from a wavefront-uniform base plus a 32-bit byte offset per lane: no
+// address arithmetic per copy on the vector unit, half the address registers.
+__device__ __forceinline__ void dma16_at(const void* base, uint32_t off, const unsigned char* dst) {
+    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const lds_void*)dst);
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(off), "s"(base), "s"(m0)
+                 : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 // ------------------------------------------------------------ limits -----
 constexpr int kMaxExperts = 1024;
 constexpr int kEntriesPerPermBlock = 512;   // (token, slot) entries per permutation block

@@ -15,9 +15,16 @@
 // panel rows as 4 x 8 tiles of v_mfma_f32_16x16x32_bf16 (fp32 accumulation;
 // it issues about 9 % faster than the 32x32x16 form on gfx950 and gives the
 // same sums);
-// operand fragments are double-buffered in registers so the LDS reads of one
-// K=32 step overlap the MFMAs of the previous one; a wavefront whose rows are
-// all past the end of a partial tile skips its MFMAs.
+// operand fragments are double-buffered in registers and the LDS reads of each
+// K=32 sub-step run among the MFMAs of the one before, across slices too: the
+// slice's only barrier sits between its two sub-steps, after which its stage is
+// refilled and the next slice's first fragments are read.  (With the barrier at
+// the slice's start, all eight wavefronts waited for 96 KiB of LDS reads with
+// the matrix units idle.  GEMM1, traced on one box: 334 -> 306 us at 4099 tokens,
+// d 2048, 64 experts, k 8, m 1024; with the 384-row panel 826 -> 768 us at 16384
+// tokens, 128 experts, m 768.  GEMM2, K = 768: unchanged, its tiles' prologue
+// and epilogue outweigh 12 slices.)  A wavefront whose rows are all past the end
+// of a partial tile only copies.
 // GEMM1's epilogue applies SwiGLU in registers (gate and up tiles of the same
 // columns live in the same lanes) and rounds H to bf16; GEMM2's epilogue scales
 // by the route weight and rounds O to bf16.  The MFMA operands are given as
@@ -37,18 +44,18 @@
 // LDS in two stages), 17 % fewer copied bytes per flop: each of the eight
 // wavefronts owns 64 token rows x 192 panel rows (192 accumulators per lane),
 // reads its A fragments once per K=32 step and its B fragments two tiles at a
-// time, double-buffered.  Per output the sums run in the same K order as the
-// 256-row panel, so H is bitwise the same; measured 2 % faster on both layer
-// shapes.
+// time, double-buffered, with the same barrier placement.  Per output the sums
+// run in the same K order as the 256-row panel, so H is bitwise the same.
 //
 // Other shapes and the fp32 path use a plain one-thread-per-output kernel.
+#include <type_traits>
+
 #include "common.h"
 
 namespace pr2 {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int BM = kTileM;      // 256 rows per tile
 constexpr int BP = 256;         // weight panel rows per tile
@@ -168,22 +175,6 @@ grouped_gemm_mfma(MfmaArgs g) {
     const int wc = wave % (BP / WN);     // panel block of WN rows
     // a wavefront whose rows are all past the tile's end only helps copy
     const bool active = wr * WM < rows;
-    // each lane's accumulators belong to MI token rows (one per MT-row block);
-    // GEMM2's route weights for them are fetched now, long before the epilogue
-    // (loads are unconditional, rows clamped into the tile, so that they all
-    // go out together rather than one masked branch at a time)
-    float gw[MI];
-    if (MODE == 1) {
-        int src[MI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) src[i] = g.perm_src[row0 + min(wr * WM + i * MT + (lane % MT), rows - 1)];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) gw[i] = g.gate[min(max(src[i], 0), g.Tk - 1)];
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-            if (wr * WM + i * MT + (lane % MT) >= rows) gw[i] = 0.0f;
-    }
-
     // DMA assignments: wavefront w copies row groups w*kGroups .. of the
     // [A rows | panel rows] tile; lane l moves row grp*kRowsPerDma + l/CHUNKS,
     // position l%CHUNKS.  A wavefront's groups all come from one tensor (the
@@ -210,7 +201,7 @@ grouped_gemm_mfma(MfmaArgs g) {
         for (int i = 0; i < kGroups; ++i) {
             const int r = wrow0 + i * kRowsPerDma + lane / CHUNKS;
             const int64_t row = MODE != 1 ? (int64_t)(min(max(rsrc[i], 0), g.Tk - 1) / g.k) : rsrc[i];
-            soff[i] = (uint32_t)(row * g.K + ((lane % CHUNKS) ^ swz(r)) * 8);
+            soff[i] = 2 * (uint32_t)(row * g.K + ((lane % CHUNKS) ^ swz(r)) * 8);
         }
     } else {
 #pragma unroll
@@ -219,26 +210,9 @@ grouped_gemm_mfma(MfmaArgs g) {
             const int pr = r - BM;
             const int64_t off = MODE != 1 ? (int64_t)(pn * 128 + (pr & 127)) * g.K
                                           : (int64_t)(pn * BP + pr) * g.K;
-            soff[i] = (uint32_t)(off + ((lane % CHUNKS) ^ swz(r)) * 8);
+            soff[i] = 2 * (uint32_t)(off + ((lane % CHUNKS) ^ swz(r)) * 8);
         }
     }
-    // A groups of 8 token rows wholly past the end of a partial tile are not
-    // copied: no stored output depends on those LDS rows (a wavefront-uniform,
-    // scalar test).  The K loop's waits are for all copies in flight (two
-    // stages: vmcnt 0), so the count issued does not matter; a deeper pipeline
-    // would count copies per stage and must not skip any.
-    static_assert(NSTAGE == 2, "the copy skip below assumes vmcnt(0) waits");
-    auto issue = [&](int stage, int k0) {
-#pragma unroll
-        for (int i = 0; i < kGroups; ++i) {
-            const int grp = wave * kGroups + i;
-            if (wrow0 < BM && wrow0 + i * kRowsPerDma >= rows) continue;
-            __builtin_amdgcn_global_load_lds((const void*)(sbase + (soff[i] + (uint32_t)k0)),
-                                             (lds_void*)&lds[stage * STAGEB + grp * 1024], 16,
-                                             0, 0);
-        }
-    };
-
     accv acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -275,45 +249,108 @@ grouped_gemm_mfma(MfmaArgs g) {
         b_base[j] = (BM + prow) * ROWB;
     }
 
-    const int nk = g.K / BK;
+    // copies of this wavefront per slice: 8, fewer (in twos: 16 rows) where its
+    // token rows run past a partial tile's end.  No stored output depends on
+    // those LDS rows.
+    const int ncopy = wrow0 >= BM ? kGroups
+                                  : min(kGroups, max(0, (rows - wrow0 + 2 * kRowsPerDma - 1) / (2 * kRowsPerDma)) * 2);
+    auto issue = [&](int stage, int k0, int q) __attribute__((always_inline)) {
+        if (ncopy <= 2 * q) return;
 #pragma unroll
-    for (int st = 0; st < NSTAGE - 1; ++st)
-        if (st < nk) issue(st, st * BK);
-    for (int kt = 0; kt < nk; ++kt) {
-        // slice kt landed (the copies of the later slices may still be in
-        // flight) and every wavefront is done with slice kt-1, whose stage is
-        // refilled next
-        if (kt + NSTAGE - 2 < nk) wait_vmcnt<(NSTAGE - 2) * kGroups>();
-        else wait_vmcnt<0>();
+        for (int i = 2 * q; i < 2 * q + 2; ++i)
+            dma16_at(sbase + k0, soff[i], &lds[stage * STAGEB + (wave * kGroups + i) * 1024]);
+    };
+    auto issue_all = [&](int stage, int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < kGroups / 2; ++q) issue(stage, k0, q);
+    };
+    // K loop, one barrier per slice.  A slice is two K=32 sub-steps; the
+    // fragments of sub-step s + 1 are read from LDS among the MFMAs of sub-step
+    // s, across slices too, so no MFMA waits for a read issued after a barrier.
+    // The barrier sits between a slice's two sub-steps: every wavefront holds the
+    // slice's last fragments by then, so the slice's stage takes the copies of
+    // slice kt + 2, and slice kt + 1 (copied for a whole slice's time) has landed.
+    static_assert(NSTAGE == 2 && NKS == 2 && MI == 4 && NJ == 8 && kGroups == 8,
+                  "K loop layout");
+    const int nk = g.K / BK;             // at least 2 (K is a multiple of 128)
+    bf16x8 fa[2][MI], fb[2][NJ];
+    auto sync = [&]() __attribute__((always_inline)) {
+        wait_vmcnt<0>();
         __syncthreads();
-        if (kt + NSTAGE - 1 < nk) issue((kt + NSTAGE - 1) % NSTAGE, (kt + NSTAGE - 1) * BK);
-        if (active) {
-            // fragments double-buffered in registers: the reads for sub-step
-            // ks+1 are in flight while the MFMAs of sub-step ks run
-            const unsigned char* base = lds + (kt % NSTAGE) * STAGEB;
-            bf16x8 fa[2][MI], fb[2][NJ];
-            auto read_frags = [&](int buf, int ks) {
+    };
+    // MFMAs of one sub-step on fragment set S; among them the copies of one
+    // slice (ISSUE) and the reads of the next sub-step's fragments (READ)
+    auto phase = [&](auto S_, auto READ, auto ISSUE, int rstage, int ks, int istage,
+                     int k0) __attribute__((always_inline)) {
+        constexpr int S = decltype(S_)::value;
+        const unsigned char* base = lds + rstage * STAGEB + kpos[ks];
+        auto read_a = [&](int i) __attribute__((always_inline)) {
+            fa[S ^ 1][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + a_base[i]));
+        };
+        auto read_b = [&](int j) __attribute__((always_inline)) {
+            fb[S ^ 1][j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + b_base[j]));
+        };
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
-                    fa[buf][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + a_base[i] + kpos[ks]));
+        for (int q = 0; q < 4; ++q) {
+            if (decltype(ISSUE)::value) issue(istage, k0, q);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    fb[buf][j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + b_base[j] + kpos[ks]));
-            };
-            read_frags(0, 0);
+            for (int j = 2 * q; j < 2 * q + 2; ++j)
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {
-                if (ks + 1 < NKS) read_frags((ks + 1) & 1, ks + 1);
-                // keep the scheduler from sinking those reads below the MFMAs
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j)
-                        acc[i][j] = mfma_bf16(fb[ks & 1][j], fa[ks & 1][i], acc[i][j]);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int i = 0; i < MI; ++i) acc[i][j] = mfma_bf16(fb[S][j], fa[S][i], acc[i][j]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (decltype(READ)::value && q < 3) {
+                if (q < 2) {
+                    read_a(2 * q);
+                    read_b(2 * q);
+                    read_a(2 * q + 1);
+                    read_b(2 * q + 1);
+                } else {
+                    read_b(4);
+                    read_b(5);
+                    read_b(6);
+                    read_b(7);
+                }
             }
         }
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    // the first two slices go out together; slice 0 is waited for alone (a plain
+    // barrier: __syncthreads() would wait for slice 1 as well)
+    issue_all(0, 0);
+    issue_all(1, BK);
+    if (ncopy == kGroups) wait_vmcnt<kGroups>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    int kt = 0;
+    if (active) {
+        const unsigned char* base = lds + kpos[0];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) fa[0][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + a_base[i]));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) fb[0][j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + b_base[j]));
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        for (; kt + 2 < nk; ++kt) {
+            phase(C0{}, C1{}, C0{}, kt & 1, 1, 0, 0);
+            sync();
+            phase(C1{}, C1{}, C1{}, (kt + 1) & 1, 0, kt & 1, (kt + 2) * BK);
+        }
+        phase(C0{}, C1{}, C0{}, kt & 1, 1, 0, 0);
+        sync();
+        phase(C1{}, C1{}, C0{}, (kt + 1) & 1, 0, 0, 0);
+        ++kt;
+        phase(C0{}, C1{}, C0{}, kt & 1, 1, 0, 0);
+        phase(C1{}, C0{}, C0{}, 0, 0, 0, 0);
+    } else {
+        // only copies, with the same barriers
+        for (; kt + 2 < nk; ++kt) {
+            sync();
+            issue_all(kt & 1, (kt + 2) * BK);
+        }
+        sync();
     }
     // Epilogue.  The MFMA computed the transposed tile (weights x tokens), so
     // accumulator element v of lane l is, for 16x16 tiles, column 4*(l/16) + v
@@ -363,6 +400,16 @@ grouped_gemm_mfma(MfmaArgs g) {
     // 8-byte pieces of 16 rows: measured 10 % faster for GEMM2 (and slower
     // for GEMM1, whose outputs are half as wide).
     // Every wavefront must be done with the operand stages first.
+    // GEMM2: the route weights of this lane's MI token rows (rows clamped into
+    // the tile, so that the loads all go out together; padding rows are not stored)
+    float gw[MI];
+    if (MODE == 1 && active) {
+        int src[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) src[i] = g.perm_src[row0 + min(wr * WM + i * MT + (lane % MT), rows - 1)];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) gw[i] = g.gate[min(max(src[i], 0), g.Tk - 1)];
+    }
     __syncthreads();
     if (!active) return;
     static_assert(MT == 16, "staged epilogue assumes 16x16 MFMA tiles");
@@ -542,37 +589,32 @@ gemm1_wide(MfmaArgs g) {
         for (int i = 0; i < kAGroupsW; ++i) {
             const int r = (wave * kAGroupsW + i) * kRowsPerDma + lane / CHUNKS;
             const int64_t row = (int64_t)(min(max(rsrc[i], 0), g.Tk - 1) / g.k);
-            soa[i] = (uint32_t)(row * g.K + ((lane % CHUNKS) ^ swz(r)) * 8);
+            soa[i] = 2 * (uint32_t)(row * g.K + ((lane % CHUNKS) ^ swz(r)) * 8);
         }
 #pragma unroll
         for (int i = 0; i < kWGroupsW; ++i) {
             const int pr = (wave * kWGroupsW + i) * kRowsPerDma + lane / CHUNKS;   // 0..191
             const uint32_t off = (uint32_t)((int64_t)(pn * (BPW / 2) + pr) * g.K);
-            sog[i] = off + ((lane % CHUNKS) ^ swz(BM + pr)) * 8;
-            sou[i] = off + ((lane % CHUNKS) ^ swz(BM + BPW / 2 + pr)) * 8;
+            sog[i] = 2 * (off + ((lane % CHUNKS) ^ swz(BM + pr)) * 8);
+            sou[i] = 2 * (off + ((lane % CHUNKS) ^ swz(BM + BPW / 2 + pr)) * 8);
         }
     }
-    static_assert(NSTAGE == 2, "the copy skip below assumes vmcnt(0) waits");
-    auto issue = [&](int stage, int k0) {
+    // copies n0 .. n1-1 of a slice: token-row groups, then gate, then up groups;
+    // a wavefront whose 32 token rows are all past a partial tile's end copies none
+    const bool acopies = wave * kAGroupsW * kRowsPerDma < rows;
+    auto issue = [&](int stage, int k0, int n0, int n1) __attribute__((always_inline)) {
         unsigned char* sb = lds + stage * STAGEBW;
 #pragma unroll
-        for (int i = 0; i < kAGroupsW; ++i) {
-            const int grp = wave * kAGroupsW + i;
-            if (grp * kRowsPerDma >= rows) continue;
-            __builtin_amdgcn_global_load_lds((const void*)(g.A + (soa[i] + (uint32_t)k0)),
-                                             (lds_void*)(sb + grp * 1024), 16, 0, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < kWGroupsW; ++i) {
-            const int grp = BM / kRowsPerDma + wave * kWGroupsW + i;
-            __builtin_amdgcn_global_load_lds((const void*)(wg + (sog[i] + (uint32_t)k0)),
-                                             (lds_void*)(sb + grp * 1024), 16, 0, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < kWGroupsW; ++i) {
-            const int grp = (BM + BPW / 2) / kRowsPerDma + wave * kWGroupsW + i;
-            __builtin_amdgcn_global_load_lds((const void*)(wu + (sou[i] + (uint32_t)k0)),
-                                             (lds_void*)(sb + grp * 1024), 16, 0, 0);
+        for (int n = n0; n < n1; ++n) {
+            if (n < kAGroupsW) {
+                if (acopies) dma16_at(g.A + k0, soa[n], sb + (wave * kAGroupsW + n) * 1024);
+            } else if (n < kAGroupsW + kWGroupsW)
+                dma16_at(wg + k0, sog[n - kAGroupsW],
+                         sb + (BM / kRowsPerDma + wave * kWGroupsW + n - kAGroupsW) * 1024);
+            else
+                dma16_at(wu + k0, sou[n - kAGroupsW - kWGroupsW],
+                         sb + ((BM + BPW / 2) / kRowsPerDma + wave * kWGroupsW + n - kAGroupsW -
+                               kWGroupsW) * 1024);
         }
     };
 
@@ -596,41 +638,82 @@ gemm1_wide(MfmaArgs g) {
     // panel row of fragment j: gate rows for j < NJW/2, the matching up rows after
     const int b0 = (BM + wc * (WNW / 2)) * ROWB;
 
-    const int nk = g.K / BK;
-    issue(0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
+    // K loop: a slice is 12 steps (two K=32 sub-steps of six panel-fragment
+    // pairs), each of 8 MFMAs.  The pair of step p + 1 is read before the MFMAs of
+    // step p, the token fragments of the next sub-step as the last pair's MFMAs
+    // release theirs, across slices too, so no MFMA waits for a read issued after
+    // a barrier.  The slice's one barrier sits before its last step: every
+    // wavefront then holds all of the slice's fragments, so the slice's stage
+    // takes the copies of slice kt + 2, and slice kt + 1 has landed.
+    static_assert(NSTAGE == 2 && NKS == 2 && NJW == 12 && MI == 4, "K loop layout");
+    constexpr int kNP = NJW / 2;                          // pairs per sub-step
+    constexpr int kCopies = kAGroupsW + 2 * kWGroupsW;    // copies per wavefront and slice
+    const int nk = g.K / BK;             // at least 2 (K is a multiple of 256)
+    bf16x8 fa[MI], fb[2][2];
+    auto read_pair = [&](int stage, int ks, int jp) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = 2 * jp + h;
+            const int prow = (j < NJW / 2 ? 0 : BPW / 2) + (j % (NJW / 2)) * MT;
+            fb[jp & 1][h] = __builtin_bit_cast(
+                bf16x8, *(const u32x4*)(lds + stage * STAGEBW + kpos[ks] + b0 + prow * ROWB));
+        }
+    };
+    auto read_a = [&](int stage, int ks, int i) __attribute__((always_inline)) {
+        fa[i] = __builtin_bit_cast(
+            bf16x8, *(const u32x4*)(lds + stage * STAGEBW + kpos[ks] + a0 + i * MT * ROWB));
+    };
+    auto sync = [&]() __attribute__((always_inline)) {
         wait_vmcnt<0>();
         __syncthreads();
-        if (kt + 1 < nk) issue((kt + 1) % NSTAGE, (kt + 1) * BK);
-        if (active) {
-            const unsigned char* base = lds + (kt % NSTAGE) * STAGEBW;
+    };
+    // one slice; NEXT: a slice follows (its first fragments are read here);
+    // ISSUE: the slice after that one is copied here
+    auto slice = [&](auto NEXT, auto ISSUE, int kt) __attribute__((always_inline)) {
+        constexpr bool next = decltype(NEXT)::value, copy = decltype(ISSUE)::value;
+        const int st = kt & 1;
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {
-                bf16x8 fa[MI], fb[2][2];
-                auto read_pair = [&](int buf, int jp) {
+        for (int p = 0; p < 2 * kNP; ++p) {
+            const int ks = p / kNP, jp = p % kNP;
+            const bool last = p == 2 * kNP - 1;
+            if (last && next) sync();
+            if (!last) read_pair(st, (p + 1) / kNP, (p + 1) % kNP);
+            else if (next) read_pair(st ^ 1, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int j = 2 * jp + h;
-                        const int prow = (j < NJW / 2 ? 0 : BPW / 2) + (j % (NJW / 2)) * MT;
-                        fb[buf][h] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + b0 + prow * ROWB + kpos[ks]));
-                    }
-                };
+            for (int i = 0; i < MI; ++i) {
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
-                    fa[i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + a0 + i * MT * ROWB + kpos[ks]));
-                read_pair(0, 0);
-#pragma unroll
-                for (int jp = 0; jp < NJW / 2; ++jp) {
-                    if (jp + 1 < NJW / 2) read_pair((jp + 1) & 1, jp + 1);
+                for (int h = 0; h < 2; ++h)
+                    acc[i][2 * jp + h] = mfma_bf16(fb[jp & 1][h], fa[i], acc[i][2 * jp + h]);
+                if (jp == kNP - 1 && (!last || next)) {
                     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-                            acc[i][2 * jp + h] = mfma_bf16(fb[jp & 1][h], fa[i], acc[i][2 * jp + h]);
+                    read_a(last ? st ^ 1 : st, last ? 0 : 1, i);
+                    if (last && copy) issue(st, (kt + 2) * BK, i * kCopies / MI, (i + 1) * kCopies / MI);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    issue(0, 0, 0, kCopies);
+    sync();
+    issue(1, BK, 0, kCopies);
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) read_a(0, 0, i);
+        read_pair(0, 0, 0);
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        int kt = 0;
+        for (; kt + 2 < nk; ++kt) slice(C1{}, C1{}, kt);
+        slice(C1{}, C0{}, kt);
+        slice(C0{}, C0{}, kt + 1);
+    } else {
+        // only copies, with the same barriers
+        for (int kt = 0; kt + 1 < nk; ++kt) {
+            sync();
+            if (kt + 2 < nk) issue(kt & 1, (kt + 2) * BK, 0, kCopies);
         }
     }
     if (!active) return;

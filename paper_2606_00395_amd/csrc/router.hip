@@ -810,7 +810,6 @@ constexpr int kRThreads = 512;            // 8 wavefronts: 2 token halves x 4 co
 constexpr int kRMaxNTW = 3;               // 16-column tiles per wavefront (<= 192 columns)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void;
 
 // Ws[kt][p * NCp + c][kk] = part p of column c at K index kt*32 + kk (zero for c >= NC).
 // Columns: folded -> W_r + A B (or W_r + A when B is null); else [W_r | A].
