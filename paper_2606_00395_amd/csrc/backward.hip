@@ -24,6 +24,8 @@
 // The router weight gradient is a separate pass over the x rows.
 // Every gradient is written exactly once (no atomics): results are
 // deterministic and overwrite the outputs.
+#include <type_traits>
+
 #include "common.h"
 
 namespace pr2 {
@@ -117,45 +119,20 @@ template <int MODE>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_gemm(BwdArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[LDSB];
-    constexpr bool kRowTiles = (MODE == DH || MODE == DX);   // C rows are permuted routes
-
-    // ---- work item
-    int nct = 1;
-    int expert, row0 = 0, rows = BM, pn = 0, rt = 0, ct = 0, klen;
-    if (kRowTiles) {
-        // XCD-aware: XCD b % 8 takes a contiguous range of the (tile, panel) list
-        const int64_t L = (int64_t)(*g.tile_count) * g.ntn;
-        const int64_t per_xcd = (L + kNumXcd - 1) / kNumXcd;
-        const int64_t local = blockIdx.x / kNumXcd;
-        if (local >= per_xcd) return;
-        const int64_t logical = (int64_t)(blockIdx.x % kNumXcd) * per_xcd + local;
-        if (logical >= L) return;
-        const int tile = (int)(logical / g.ntn);
-        pn = (int)(logical % g.ntn);
-        expert = g.tiles[3 * tile + 0];
-        row0 = g.tiles[3 * tile + 1];
-        rows = g.tiles[3 * tile + 2];
-        klen = MODE == DH ? g.d : 2 * g.m;
-    } else {
-        // Token-contracted: an item's cost grows with its expert's route count.
-        // Experts are dealt to the XCDs round-robin in decreasing count order and
-        // each XCD runs its experts' output tiles biggest first (the dispatcher
-        // starts workgroups in index order), so the busiest experts neither pile
-        // up on one XCD nor start last.
-        const int nrt = MODE == WD ? g.d / BM : 2 * g.m / BM;
-        nct = MODE == WD ? (g.m + BN - 1) / BN : g.d / BN;
-        const int per_e = nrt * nct;
-        const int xcd = blockIdx.x % kNumXcd;
-        const int local = blockIdx.x / kNumXcd;
-        const int slot = local / per_e;
-        if (xcd + kNumXcd * slot >= g.N) return;
-        expert = g.order[xcd + kNumXcd * slot];
-        const int tt = local % per_e;
-        rt = tt / nct;
-        ct = tt % nct;
-        row0 = g.offsets[expert];
-        klen = g.offsets[expert + 1] - row0;
-    }
+    // ---- work item.  XCD-aware: XCD b % 8 takes a contiguous range of the
+    // (tile, panel) list
+    const int64_t L = (int64_t)(*g.tile_count) * g.ntn;
+    const int64_t per_xcd = (L + kNumXcd - 1) / kNumXcd;
+    const int64_t local = blockIdx.x / kNumXcd;
+    if (local >= per_xcd) return;
+    const int64_t logical = (int64_t)(blockIdx.x % kNumXcd) * per_xcd + local;
+    if (logical >= L) return;
+    const int tile = (int)(logical / g.ntn);
+    const int pn = (int)(logical % g.ntn);
+    const int expert = g.tiles[3 * tile + 0];
+    const int row0 = g.tiles[3 * tile + 1];
+    const int rows = g.tiles[3 * tile + 2];
+    const int klen = MODE == DH ? g.d : 2 * g.m;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -163,22 +140,21 @@ bwd_gemm(BwdArgs g) {
     const int wr = wave >> 1;            // 64-row block of the output tile
     const int wc = wave & 1;             // 128-column block
     const int half = wave >> 2;          // operand this wavefront loads: 0 rows, 1 columns
-    // DH and WD have m columns, a multiple of 128: the last panel may hold 128.
-    // Its copies then read its 128 columns twice (nothing is read past a row's
-    // end) and the wavefronts of its upper half only help copy.
-    const int ncols = MODE == DH ? min(BN, g.m - pn * BN) : MODE == WD ? min(BN, g.m - ct * BN) : BN;
+    // DH has m columns, a multiple of 128: the last panel may hold 128.  Its
+    // copies then read its 128 columns twice (nothing is read past a row's end)
+    // and the wavefronts of its upper half only help copy.
+    const int ncols = MODE == DH ? min(BN, g.m - pn * BN) : BN;
     const bool active = wr * WM < rows && wc * WN < ncols;
 
     // ---- operand loading.  Both operands are copied global -> LDS with
     // 16-byte direct-to-LDS loads; wavefronts 0-3 copy the row operand (C
     // rows), 4-7 the column operand.  A K-contiguous operand (the gathered dy
     // rows of DH, the da | du rows of DX) is stored as 256 tile rows of 128
-    // bytes (64 K values), 16-byte chunks XOR-swizzled per row.  A K-strided
-    // operand (the weights of DH and DX, both operands of WD and WGU) is
-    // stored K-major: 64 K rows of 512 bytes (the tile's 256 columns), chunk c
-    // of K row kr at position c ^ 4 (kr & 3).  Both forms fill 32 KiB.
-    constexpr bool kStridedA = (MODE == WD || MODE == WGU);
-    const bool strided = half == 1 || kStridedA;
+    // bytes (64 K values), 16-byte chunks XOR-swizzled per row.  The K-strided
+    // weights are stored K-major: 64 K rows of 512 bytes (the tile's 256
+    // columns), chunk c of K row kr at position c ^ 4 (kr & 3).  Both forms fill
+    // 32 KiB.
+    const bool strided = half == 1;
     const int wq = wave & 3;
     const int64_t ew = (int64_t)expert * g.m * g.d;      // elements per expert matrix
 
@@ -186,88 +162,40 @@ bwd_gemm(BwdArgs g) {
     // wavefront moves tile rows 8 (8 wq + i) .. +7
     const bf16_t* sbase = MODE == DH ? g.dy : g.AU;
     uint32_t soff[kGroups];
-    if (!kStridedA) {
 #pragma unroll
-        for (int i = 0; i < kGroups; ++i) {
-            const int r = wq * (kGroups * 8) + i * 8 + lane / 8;
-            const int chunk = (lane % 8) ^ swz(r);
-            const int rr = r < rows ? r : 0;
-            uint32_t off;
-            if (MODE == DH)
-                off = (uint32_t)(min(max(g.perm_src[row0 + rr], 0), g.Tk - 1) / g.k) * (uint32_t)g.d;
-            else
-                off = (uint32_t)(row0 + rr) * (uint32_t)(2 * g.m);
-            soff[i] = off + chunk * 8;
-        }
+    for (int i = 0; i < kGroups; ++i) {
+        const int r = wq * (kGroups * 8) + i * 8 + lane / 8;
+        const int chunk = (lane % 8) ^ swz(r);
+        const int rr = r < rows ? r : 0;
+        uint32_t off;
+        if (MODE == DH)
+            off = (uint32_t)(min(max(g.perm_src[row0 + rr], 0), g.Tk - 1) / g.k) * (uint32_t)g.d;
+        else
+            off = (uint32_t)(row0 + rr) * (uint32_t)(2 * g.m);
+        soff[i] = off + chunk * 8;
     }
     // K-strided: copy instruction i of this wavefront moves K rows
     // k0 + 2 i (lanes 0-31) and k0 + 2 i + 1 (lanes 32-63) of the slice,
     // k0 = 16 wq; lane l lands at chunk position l % 32 and so loads chunk
     // (l % 32) ^ 4 ((2 i + l / 32) & 3) of its K row: one column pattern for
-    // even i, one for odd.  Rows at or past klen read zeros.  The two rows of
-    // a copy are the same for the whole wavefront, so their addresses are
-    // formed on the scalar unit and each lane only adds its own offset.
+    // even i, one for odd.  The row addresses are the same for the whole
+    // wavefront and formed on the scalar unit.
     const int hi = lane >> 5;
-    const int cmask = half == 1 && ncols < BN ? WN - 1 : BN - 1;
+    const int cmask = ncols < BN ? WN - 1 : BN - 1;
     const int cpat[2] = {(8 * ((lane & 31) ^ (4 * hi))) & cmask,
                          (8 * ((lane & 31) ^ (4 * (hi + 2)))) & cmask};
-    constexpr bool kHasGather = (MODE == WD || MODE == WGU);
-    const bool gathered = (MODE == WD && half == 0) || (MODE == WGU && half == 1);
-    // plain strided operand: K row 0 at this tile's columns, row stride ld
-    const bf16_t* rbase = nullptr;
-    int64_t ld = 0;
-    if (MODE == DH) { rbase = g.Wd + ew + pn * BN; ld = g.m; }
-    if (MODE == DX) { rbase = g.Wg + ew + pn * BN; ld = g.d; }
-    if (MODE == WD) { rbase = g.Hg + (int64_t)row0 * g.m + ct * BN; ld = g.m; }
-    if (MODE == WGU) { rbase = g.AU + (int64_t)row0 * (2 * g.m) + rt * BM; ld = 2 * g.m; }
+    const bf16_t* const rbase = (MODE == DH ? g.Wd : g.Wg) + ew + pn * BN;
+    const int64_t ld = MODE == DH ? g.m : g.d;
     const int64_t loff[2] = {hi * ld + cpat[0], hi * ld + cpat[1]};
-    // gathered operand (WD: dy rows, WGU: x rows): lane l holds the route
-    // entry of K row 16 wq + l % 16 of the next slice, loaded one slice ahead
-    // (rows past klen load the expert's last entry and copy zeros)
-    const bf16_t* gbase = MODE == WD ? g.dy + rt * BM : g.x + ct * BN;
-    int gent = 0;
-    auto fetch_tok = [&](int kt) __attribute__((always_inline)) {
-        gent = g.perm_src[row0 + min(kt * BK + 16 * wq + (lane & 15), klen - 1)];
-    };
-    // token row of a route entry t k + s: multiply-high by kmul = ceil(2^32 / k)
-    // is exact for entries below 2^32 / k (checked on the host); k = 1 has kmul 0
-    auto tok_of = [&](int e) __attribute__((always_inline)) {
-        const uint32_t n = (uint32_t)min(max(e, 0), g.Tk - 1);
-        return (int64_t)(__umulhi(n, g.kmul) + (g.kmul == 0u ? n : 0u));
-    };
-    auto issue_strided = [&](int stage, int kt) __attribute__((always_inline)) {
-        unsigned char* dst = lds + stage * STAGEB + (half ? BM * ROWB : 0) + wq * (16 * 512);
-        const int k0 = kt * BK + 16 * wq;
-        const bool full = kt * BK + BK <= klen;
-        if (kHasGather && gathered) {
-#pragma unroll
-            for (int i = 0; i < kGroups; ++i) {
-                const int ka = k0 + 2 * i;
-                const bf16_t* pa = ka < klen ? gbase + tok_of(__builtin_amdgcn_readlane(gent, 2 * i)) * g.d : kZeroRow;
-                const bf16_t* pb =
-                    ka + 1 < klen ? gbase + tok_of(__builtin_amdgcn_readlane(gent, 2 * i + 1)) * g.d : kZeroRow;
-                dma16((hi ? pb : pa) + cpat[i & 1], dst + i * 1024);
-            }
-        } else {
-            const bf16_t* rb = rbase;
-            int kr = k0;
-            if (MODE == DX && kt * BK >= g.m) { rb = g.Wu + ew + pn * BN; kr -= g.m; }
-            const bf16_t* p = rb + (int64_t)kr * ld;
-            if (kHasGather && !full) {
-#pragma unroll
-                for (int i = 0; i < kGroups; ++i)
-                    dma16(k0 + 2 * i + hi < klen ? p + 2 * i * ld + loff[i & 1] : kZeroRow + cpat[i & 1],
-                          dst + i * 1024);
-            } else {
-#pragma unroll
-                for (int i = 0; i < kGroups; ++i) dma16(p + 2 * i * ld + loff[i & 1], dst + i * 1024);
-            }
-        }
-    };
     auto issue = [&](int stage, int kt) __attribute__((always_inline)) {
         if (strided) {
-            issue_strided(stage, kt);
-            if (kHasGather && gathered && kt + 1 < (klen + BK - 1) / BK) fetch_tok(kt + 1);
+            unsigned char* dst = lds + stage * STAGEB + BM * ROWB + wq * (16 * 512);
+            const bf16_t* rb = rbase;
+            int kr = kt * BK + 16 * wq;
+            if (MODE == DX && kt * BK >= g.m) { rb = g.Wu + ew + pn * BN; kr -= g.m; }
+            const bf16_t* p = rb + (int64_t)kr * ld;
+#pragma unroll
+            for (int i = 0; i < kGroups; ++i) dma16(p + 2 * i * ld + loff[i & 1], dst + i * 1024);
         } else {
 #pragma unroll
             for (int i = 0; i < kGroups; ++i) {
@@ -305,16 +233,12 @@ bwd_gemm(BwdArgs g) {
     auto tr_pos = [&](int cb) { return kl * 512 + ((((cb >> 3) ^ tsw)) << 4) + ((nl & 4) << 1); };
     int a_pos[MI], b_pos[NJ];
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
-        a_pos[i] = kStridedA ? tr_pos(wr * WM + i * 32) : (wr * WM + i * 32) * ROWB;
+    for (int i = 0; i < MI; ++i) a_pos[i] = (wr * WM + i * 32) * ROWB;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) b_pos[j] = BM * ROWB + tr_pos(wc * WN + j * 32);
 
     const int nk = (klen + BK - 1) / BK;
-    if (nk > 0) {
-        if (kHasGather && gathered) fetch_tok(0);
-        issue(0, 0);
-    }
+    issue(0, 0);
     for (int kt = 0; kt < nk; ++kt) {
         wait_vmcnt<0>();
         __syncthreads();
@@ -332,8 +256,7 @@ bwd_gemm(BwdArgs g) {
             auto read_frags = [&](int buf, int ks) __attribute__((always_inline)) {
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
-                    fa[buf][i] = kStridedA ? tr_frag(a_pos[i], ks)
-                                           : __builtin_bit_cast(bf16x8, *(const u32x4*)(base + a_pos[i] + kpos[ks]));
+                    fa[buf][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + a_pos[i] + kpos[ks]));
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) fb[buf][j] = tr_frag(b_pos[j], ks);
             };
@@ -355,16 +278,15 @@ bwd_gemm(BwdArgs g) {
     // ---- epilogues.  Lane l holds output row l%32 of each 32-row block and
     // columns 8*(v/4) + 4*(l/32) + v%4 of each 32-column block.
     const int ncol0 = 4 * (lane >> 5);
-    if (MODE != DH) {
-        // DX (bf16 rows) and WD / WGU (fp32 rows) are staged through this
-        // wavefront's share of the freed LDS stages (16-byte chunks XOR-swizzled
-        // by row; for bf16 the 8-byte halves of a chunk are also swapped in rows
-        // with bit 3 set, so the 16 rows of one 8-byte write cycle hit distinct
-        // banks) and stored 16 bytes per lane along whole row segments,
-        // instead of 8- or 16-byte pieces of 32 rows per store
+    if (MODE == DX) {
+        // staged through this wavefront's share of the freed LDS stages (16-byte
+        // chunks XOR-swizzled by row; the 8-byte halves of a chunk are also
+        // swapped in rows with bit 3 set, so the 16 rows of one 8-byte write cycle
+        // hit distinct banks) and stored 16 bytes per lane along whole row
+        // segments, instead of 8-byte pieces of 32 rows per store
         __syncthreads();
         if (!active) return;
-        if (MODE == DX) {
+        {
             constexpr int RB = WN * 2, NCH = RB / 16;        // 256-byte staged rows
             unsigned char* sw = lds + wave * (WM * RB);
 #pragma unroll
@@ -393,41 +315,6 @@ bwd_gemm(BwdArgs g) {
                 if (row & 8) v = u32x4{v[2], v[3], v[0], v[1]};
                 if (r < rows)
                     *(u32x4*)(g.dxr + ((int64_t)row0 + r) * g.d + pn * BN + wc * WN + ch * 8) = v;
-            }
-        } else {
-            // fp32: 512-byte staged rows, one 32-row block at a time
-            constexpr int RB = WN * 4, NCH = RB / 16;
-            unsigned char* sw = lds + wave * (32 * RB);
-            const int64_t ew = (int64_t)expert * g.m * g.d;
-#pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                const int row = lane & 31;
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                    for (int a4 = 0; a4 < 4; ++a4) {
-                        const int col = j * 32 + 8 * a4 + ncol0;
-                        const int v0 = 4 * a4;
-                        *(f32x4*)(sw + row * RB + (((col >> 2) ^ (row & (NCH - 1))) << 4)) =
-                            f32x4{acc[i][j][v0], acc[i][j][v0 + 1], acc[i][j][v0 + 2], acc[i][j][v0 + 3]};
-                    }
-                __builtin_amdgcn_s_waitcnt(0xc07f);
-                __builtin_amdgcn_wave_barrier();
-                const int ch = lane % NCH;
-#pragma unroll
-                for (int p = 0; p < 32 / (64 / NCH); ++p) {
-                    const int row2 = p * (64 / NCH) + lane / NCH;
-                    const int R = rt * BM + wr * WM + i * 32 + row2;
-                    float* orow;
-                    if (MODE == WD) orow = g.dWd + ew + (int64_t)R * g.m;
-                    else orow = (R < g.m ? g.dWg + ew + (int64_t)R * g.d
-                                         : g.dWu + ew + (int64_t)(R - g.m) * g.d);
-                    *(u32x4*)(orow + ct * BN + wc * WN + ch * 4) =
-                        *(const u32x4*)(sw + row2 * RB + ((ch ^ (row2 & (NCH - 1))) << 4));
-                }
-                // the next block overwrites the region
-                __builtin_amdgcn_s_waitcnt(0xc07f);
-                __builtin_amdgcn_wave_barrier();
             }
         }
         return;
@@ -522,6 +409,270 @@ bwd_gemm(BwdArgs g) {
             __builtin_amdgcn_s_waitcnt(0xc07f);
             __builtin_amdgcn_wave_barrier();
         }
+    }
+}
+
+// Weight gradients: C = A^T B contracted over an expert's routes,
+//   WD   dW_down[e] = (gathered dy)^T (g H),   WGU  dW_gate | dW_up [e] = (da | du)^T (gathered x).
+// Both operands run along K rows of 512 bytes (the tile's 256 columns), so K
+// advances in steps of 32 rows (32 KiB) through a ring of four LDS stages: while
+// step h is multiplied, steps h + 2 and h + 3 are in flight, and the copies never
+// drain at a barrier (the loop waits for a count of its copies, not for all).
+// With two 64-row stages the copies of one slice had to land before the next
+// were issued, and these loops are short (an expert's routes: 16 such slices at
+// 1024 routes) with a gathered operand.
+// The barrier of a step sits between its two K=16 sub-steps: every wavefront
+// holds the step's last fragments then, so its stage takes the copies of step
+// h + 4 and the fragments of step h + 1 are read among the MFMAs.
+// The gathered operand's row offsets are put into LDS once per tile (8192 routes
+// at a time); K rows past the last route read zeros in the plain operand and the
+// expert's last route in the gathered one.
+constexpr int kWgBK = 32;                          // K rows per step
+constexpr int kWgStages = 4;
+constexpr int kWgOpB = kWgBK * 512;                // bytes per operand and step
+constexpr int kWgStageB = 2 * kWgOpB;              // 32 KiB
+constexpr int kWgRoutes = 8192;                    // route offsets held in LDS
+constexpr int kWgCopies = kWgBK / 2 / 4;           // copies per wavefront and step (2 K rows each)
+
+template <int MODE>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+bwd_wgrad(BwdArgs g) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kWgStages * kWgStageB];
+    __shared__ __attribute__((aligned(16))) uint32_t roff[kWgRoutes];
+    static_assert(MODE == WD || MODE == WGU, "weight-gradient modes");
+
+    // Work item: its cost grows with its expert's route count.  Experts are
+    // dealt to the XCDs round-robin in decreasing count order and each XCD runs
+    // its experts' output tiles biggest first (the dispatcher starts workgroups
+    // in index order), so the busiest experts neither pile up on one XCD nor
+    // start last.
+    const int nrt = MODE == WD ? g.d / BM : 2 * g.m / BM;
+    const int nct = MODE == WD ? (g.m + BN - 1) / BN : g.d / BN;
+    const int per_e = nrt * nct;
+    const int xcd = blockIdx.x % kNumXcd;
+    const int local = blockIdx.x / kNumXcd;
+    const int slot = local / per_e;
+    if (xcd + kNumXcd * slot >= g.N) return;
+    const int expert = __builtin_amdgcn_readfirstlane(g.order[xcd + kNumXcd * slot]);
+    const int rt = local % per_e / nct;
+    const int ct = local % per_e % nct;
+    const int row0 = __builtin_amdgcn_readfirstlane(g.offsets[expert]);
+    const int klen = __builtin_amdgcn_readfirstlane(g.offsets[expert + 1]) - row0;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1;            // 64-row block of the output tile
+    const int wc = wave & 1;             // 128-column block
+    const int half = wave >> 2;          // operand this wavefront copies: 0 rows, 1 columns
+    const int wq = wave & 3;
+    // WD has m columns, a multiple of 128: the last panel may hold 128.  Its
+    // copies then read those twice and the wavefronts of its upper half only copy.
+    const int ncols = MODE == WD ? min(BN, g.m - ct * BN) : BN;
+    const bool active = wc * WN < ncols;
+    const int64_t ew = (int64_t)expert * g.m * g.d;
+
+    // Copy i of this wavefront moves K rows 8 wq + 2 i (lanes 0-31) and + 1
+    // (lanes 32-63) of the step; chunk c of K row kr is stored at c ^ 4 (kr & 3),
+    // so lane l loads chunk (l % 32) ^ 4 ((2 i + l / 32) & 3).
+    const bool gathered = half == (MODE == WD ? 0 : 1);
+    const int hi = lane >> 5;
+    const int cmask = half == 1 && ncols < BN ? WN - 1 : BN - 1;
+    const int cpat[2] = {(8 * ((lane & 31) ^ (4 * hi))) & cmask,
+                         (8 * ((lane & 31) ^ (4 * (hi + 2)))) & cmask};
+    const bf16_t* const gbase = MODE == WD ? g.dy + rt * BM : g.x + ct * BN;
+    const int ld = MODE == WD ? g.m : 2 * g.m;
+    const bf16_t* const pbase = MODE == WD ? g.Hg + (int64_t)row0 * g.m + ct * BN
+                                           : g.AU + (int64_t)row0 * (2 * g.m) + rt * BM;
+    const uint32_t poff[2] = {2u * (uint32_t)(hi * ld + cpat[0]), 2u * (uint32_t)(hi * ld + cpat[1])};
+    // token row of a route entry t k + s: multiply-high by kmul = ceil(2^32 / k)
+    // is exact for entries below 2^32 / k (checked on the host); k = 1 has kmul 0
+    auto tok_of = [&](int e) __attribute__((always_inline)) {
+        const uint32_t n = (uint32_t)min(max(e, 0), g.Tk - 1);
+        return __umulhi(n, g.kmul) + (g.kmul == 0u ? n : 0u);
+    };
+
+    f32x16 acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    // MFMA fragments by two transposing reads each, as in bwd_gemm
+    const int s16 = lane & 15, g4 = lane >> 4;
+    const int nl = 16 * (g4 & 1) + 4 * (s16 & 3);
+    const int kl = 8 * (g4 >> 1) + (s16 >> 2);
+    const int tsw = (nl >> 3) ^ (4 * (kl & 3));
+    auto tr_pos = [&](int cb) { return kl * 512 + ((((cb >> 3) ^ tsw)) << 4) + ((nl & 4) << 1); };
+    int a_pos[MI], b_pos[NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a_pos[i] = tr_pos(wr * WM + i * 32);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b_pos[j] = kWgOpB + tr_pos(wc * WN + j * 32);
+
+    for (int kc = 0; kc < klen; kc += kWgRoutes) {
+        const int clen = min(kWgRoutes, klen - kc);
+        const int nh = (clen + kWgBK - 1) / kWgBK;
+        uint32_t go[kWgCopies];          // gathered rows' byte offsets of the next step to copy
+        auto fetch = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kWgCopies; ++i) go[i] = roff[h * kWgBK + 8 * wq + 2 * i + hi];
+        };
+        auto issue_gathered = [&](int h) __attribute__((always_inline)) {
+            unsigned char* dst = lds + (h % kWgStages) * kWgStageB + half * kWgOpB + wq * 4096;
+#pragma unroll
+            for (int i = 0; i < kWgCopies; ++i)
+                dma16_at(gbase, go[i] + 2u * (uint32_t)cpat[i & 1], dst + i * 1024);
+        };
+        auto issue_plain = [&](int h) __attribute__((always_inline)) {
+            unsigned char* dst = lds + (h % kWgStages) * kWgStageB + half * kWgOpB + wq * 4096;
+            const int k0 = h * kWgBK + 8 * wq;
+            const bf16_t* p = pbase + (int64_t)(kc + k0) * ld;
+            if ((h + 1) * kWgBK <= clen) {
+#pragma unroll
+                for (int i = 0; i < kWgCopies; ++i) dma16_at(p + 2 * i * ld, poff[i & 1], dst + i * 1024);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kWgCopies; ++i)
+                    dma16(k0 + 2 * i + hi < clen ? p + (2 * i + hi) * ld + cpat[i & 1] : kZeroRow + cpat[i & 1],
+                          dst + i * 1024);
+            }
+        };
+        auto barrier = [&]() __attribute__((always_inline)) {
+            // a plain barrier: __syncthreads() would wait for every copy in flight
+            __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::: "memory");
+        };
+        // the last chunk's readers of roff and of the stages are done
+        if (kc > 0) barrier();
+        if (gathered) {
+            for (int q = wq * 64 + lane; q < nh * kWgBK; q += 256)
+                roff[q] = tok_of(g.perm_src[row0 + kc + min(q, clen - 1)]) * (uint32_t)(2 * g.d);
+        } else {
+            for (int h = 0; h < min(nh, kWgStages); ++h) issue_plain(h);
+        }
+        barrier();
+        if (gathered) {
+            for (int h = 0; h < min(nh, kWgStages); ++h) {
+                fetch(h);
+                issue_gathered(h);
+            }
+            if (nh > kWgStages) fetch(kWgStages);
+        }
+        // at most n steps' copies may still be in flight
+        auto wait_steps = [&](int n) __attribute__((always_inline)) {
+            if (n >= 3) wait_vmcnt<3 * kWgCopies>();
+            else if (n == 2) wait_vmcnt<2 * kWgCopies>();
+            else if (n == 1) wait_vmcnt<kWgCopies>();
+            else wait_vmcnt<0>();
+        };
+        wait_steps(min(nh, kWgStages) - 1);
+        barrier();
+
+        bf16x8 fa[2][MI], fb[2][NJ];
+        auto tr_frag = [&](const unsigned char* p) __attribute__((always_inline)) {
+            const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
+            const v4s hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 4 * 512));
+            return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
+        };
+        // MFMAs on fragment set S, and among them the reads of sub-step ks of
+        // the given stage into the other set
+        auto phase = [&](auto S_, int stage, int ks) __attribute__((always_inline)) {
+            constexpr int S = decltype(S_)::value;
+            const unsigned char* base = lds + stage * kWgStageB + ks * (16 * 512);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[S][j], fa[S][i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (j == 0) {
+                    fa[S ^ 1][0] = tr_frag(base + a_pos[0]);
+                    fa[S ^ 1][1] = tr_frag(base + a_pos[1]);
+                } else if (j < 3) {
+                    fb[S ^ 1][2 * j - 2] = tr_frag(base + b_pos[2 * j - 2]);
+                    fb[S ^ 1][2 * j - 1] = tr_frag(base + b_pos[2 * j - 1]);
+                }
+            }
+        };
+        using C0 = std::integral_constant<int, 0>;
+        using C1 = std::integral_constant<int, 1>;
+        // step h's stage is free: copy step h + kWgStages into it
+        auto refill = [&](int h) __attribute__((always_inline)) {
+            if (h + kWgStages >= nh) return;
+            if (gathered) {
+                issue_gathered(h + kWgStages);
+                if (h + kWgStages + 1 < nh) fetch(h + kWgStages + 1);
+            } else {
+                issue_plain(h + kWgStages);
+            }
+        };
+        if (active) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) fa[0][i] = tr_frag(lds + a_pos[i]);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) fb[0][j] = tr_frag(lds + b_pos[j]);
+            for (int h = 0; h < nh; ++h) {
+                phase(C0{}, h % kWgStages, 1);
+                wait_steps(min(nh - 1, h + kWgStages - 1) - (h + 1));
+                barrier();
+                refill(h);
+                // (past the last step the reads fetch an old stage; unused)
+                phase(C1{}, (h + 1) % kWgStages, 0);
+            }
+        } else {
+            for (int h = 0; h < nh; ++h) {
+                wait_steps(min(nh - 1, h + kWgStages - 1) - (h + 1));
+                barrier();
+                refill(h);
+            }
+        }
+    }
+    // Lane l holds output row l%32 of each 32-row block and columns 8*(v/4) +
+    // 4*(l/32) + v%4 of each 32-column block.  fp32 rows are staged through this
+    // wavefront's share of the freed stages, one 32-row block at a time, and
+    // stored 16 bytes per lane along whole row segments.
+    const int ncol0 = 4 * (lane >> 5);
+    __syncthreads();
+    if (!active) return;
+    constexpr int RB = WN * 4, NCH = RB / 16;
+    unsigned char* sw = lds + wave * (32 * RB);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int row = lane & 31;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int a4 = 0; a4 < 4; ++a4) {
+                const int col = j * 32 + 8 * a4 + ncol0;
+                const int v0 = 4 * a4;
+                *(f32x4*)(sw + row * RB + (((col >> 2) ^ (row & (NCH - 1))) << 4)) =
+                    f32x4{acc[i][j][v0], acc[i][j][v0 + 1], acc[i][j][v0 + 2], acc[i][j][v0 + 3]};
+            }
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __builtin_amdgcn_wave_barrier();
+        const int ch = lane % NCH;
+#pragma unroll
+        for (int p = 0; p < 32 / (64 / NCH); ++p) {
+            const int row2 = p * (64 / NCH) + lane / NCH;
+            const int R = rt * BM + wr * WM + i * 32 + row2;
+            float* orow;
+            if (MODE == WD) orow = g.dWd + ew + (int64_t)R * g.m;
+            else orow = (R < g.m ? g.dWg + ew + (int64_t)R * g.d
+                                 : g.dWu + ew + (int64_t)(R - g.m) * g.d);
+            *(u32x4*)(orow + ct * BN + wc * WN + ch * 4) =
+                *(const u32x4*)(sw + row2 * RB + ((ch ^ (row2 & (NCH - 1))) << 4));
+        }
+        // the next block overwrites the region
+        __builtin_amdgcn_s_waitcnt(0xc07f);
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -1441,7 +1592,7 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
         const int64_t experts_per_xcd = (d.N + kNumXcd - 1) / kNumXcd;
         {
             LaunchScope scope("bwd_wgrad_down", s);
-            hipLaunchKernelGGL(bwd_gemm<WD>,
+            hipLaunchKernelGGL(bwd_wgrad<WD>,
                                dim3((unsigned)(kNumXcd * experts_per_xcd * (d.d / BM) *
                                                ((d.m + BN - 1) / BN))),
                                dim3(kThreads), 0, s, g);
@@ -1449,7 +1600,7 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
         if ((e = hipGetLastError()) != hipSuccess) return e;
         {
             LaunchScope scope("bwd_wgrad_gate_up", s);
-            hipLaunchKernelGGL(bwd_gemm<WGU>,
+            hipLaunchKernelGGL(bwd_wgrad<WGU>,
                                dim3((unsigned)(kNumXcd * experts_per_xcd * (2 * d.m / BM) * (d.d / BN))),
                                dim3(kThreads), 0, s, g);
         }

@@ -322,9 +322,11 @@ grouped_gemm_mfma(MfmaArgs g) {
     issue_all(1, BK);
     if (ncopy == kGroups) wait_vmcnt<kGroups>();
     else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
     int kt = 0;
     if (active) {
         const unsigned char* base = lds + kpos[0];
