@@ -14,13 +14,13 @@
 //   dp_ts = g_ts (dg_ts - sum_s' g_ts' dg_ts'),  dW_r[:, e] = sum_q X dp,  db_r[e] = sum_q dp
 //
 // bf16 path: four grouped GEMMs on v_mfma_f32_32x32x16_bf16 with the tile
-// shape of the forward kernels (256 x 256 output tile, K slices of 64, two
-// LDS stages, eight wavefronts of 64 x 128), every operand copied global ->
-// LDS by 16-byte direct-to-LDS loads.  An operand whose K index runs along
-// its rows in memory (the weights in the input-gradient GEMMs, both operands
-// of the token-contracted weight-gradient GEMMs) is kept K-major in LDS and
-// its MFMA fragments are read with the transposing LDS read of gfx950
-// (ds_read_b64_tr_b16), so no operand passes through registers on its way in.
+// shape of the forward kernels (256 x 256 output tile, eight wavefronts of
+// 64 x 128), every operand copied global -> LDS by 16-byte direct-to-LDS loads.
+// An operand whose K index runs along its rows in memory (the weights in the
+// input-gradient GEMMs, both operands of the token-contracted weight-gradient
+// GEMMs) is kept K-major in LDS and its MFMA fragments are read with the
+// transposing LDS read of gfx950 (ds_read_b64_tr_b16), so no operand passes
+// through registers on its way in.
 // The router weight gradient is a separate pass over the x rows.
 // Every gradient is written exactly once (no atomics): results are
 // deterministic and overwrite the outputs.
@@ -37,16 +37,15 @@ typedef __attribute__((address_space(3))) v4s lds_v4s;
 
 constexpr int BM = 256;         // output tile rows
 constexpr int BN = 256;         // output tile columns
-constexpr int BK = 64;          // K slice
-constexpr int ROWB = BK * 2;    // bytes per LDS row
-constexpr int NSTAGE = 2;
+constexpr int kBK = 32;         // K per step
+constexpr int kStages = 4;      // LDS stages (steps)
 constexpr int WM = 64, WN = 128;
 constexpr int MI = WM / 32, NJ = WN / 32;
 constexpr int NWAVE = 8;
 constexpr int kThreads = 64 * NWAVE;
-constexpr int kGroups = 8;      // 8-row DMA groups per wavefront (4 wavefronts x 64 rows)
-constexpr int STAGEB = (BM + BN) * ROWB;
-constexpr int LDSB = NSTAGE * STAGEB;
+constexpr int kOpB = kBK * 512;                 // bytes per operand and step (16 KiB)
+constexpr int kStageB = 2 * kOpB;
+constexpr int kCopies = 4;      // copies per wavefront and step
 constexpr int kNumXcd = 8;
 
 enum { DH = 0, DX = 1, WD = 2, WGU = 3 };
@@ -76,7 +75,10 @@ struct BwdArgs {
     float* dWd;
 };
 
-__device__ __forceinline__ int swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+// 16-byte chunk c of a 64-byte LDS row r sits at position c ^ rswz(r): the eight
+// rows of one cycle of a 16-byte fragment read, two neighbouring chunks each,
+// then hit distinct banks
+__device__ __forceinline__ int rswz(int r) { return (r >> 1) & 2; }
 
 template <int n>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -118,7 +120,7 @@ __device__ __attribute__((aligned(16))) const bf16_t kZeroRow[BN] = {};
 template <int MODE>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_gemm(BwdArgs g) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[LDSB];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kStages * kStageB];
     // ---- work item.  XCD-aware: XCD b % 8 takes a contiguous range of the
     // (tile, panel) list
     const int64_t L = (int64_t)(*g.tile_count) * g.ntn;
@@ -146,62 +148,58 @@ bwd_gemm(BwdArgs g) {
     const int ncols = MODE == DH ? min(BN, g.m - pn * BN) : BN;
     const bool active = wr * WM < rows && wc * WN < ncols;
 
-    // ---- operand loading.  Both operands are copied global -> LDS with
-    // 16-byte direct-to-LDS loads; wavefronts 0-3 copy the row operand (C
-    // rows), 4-7 the column operand.  A K-contiguous operand (the gathered dy
-    // rows of DH, the da | du rows of DX) is stored as 256 tile rows of 128
-    // bytes (64 K values), 16-byte chunks XOR-swizzled per row.  The K-strided
-    // weights are stored K-major: 64 K rows of 512 bytes (the tile's 256
-    // columns), chunk c of K row kr at position c ^ 4 (kr & 3).  Both forms fill
-    // 32 KiB.
-    const bool strided = half == 1;
+    // ---- operand loading.  K advances in steps of 32 through a ring of four LDS
+    // stages (32 KiB each).  Wavefronts 0-3 copy the row operand (C rows: the
+    // gathered dy rows of DH, the da | du rows of DX), 256 rows of 64 bytes per
+    // step, 16-byte chunk c of row r at position c ^ rswz(r); wavefronts 4-7 the
+    // weights, K-major: 32 K rows of 512 bytes (the tile's 256 columns), chunk c
+    // of K row kr at position c ^ 4 (kr & 3).  Each issues four copies a step.
     const int wq = wave & 3;
     const int64_t ew = (int64_t)expert * g.m * g.d;      // elements per expert matrix
 
-    // K-contiguous rows (DH: gathered dy, DX: da | du): copy group i of this
-    // wavefront moves tile rows 8 (8 wq + i) .. +7
-    const bf16_t* sbase = MODE == DH ? g.dy : g.AU;
-    uint32_t soff[kGroups];
-#pragma unroll
-    for (int i = 0; i < kGroups; ++i) {
-        const int r = wq * (kGroups * 8) + i * 8 + lane / 8;
-        const int chunk = (lane % 8) ^ swz(r);
-        const int rr = r < rows ? r : 0;
-        uint32_t off;
-        if (MODE == DH)
-            off = (uint32_t)(min(max(g.perm_src[row0 + rr], 0), g.Tk - 1) / g.k) * (uint32_t)g.d;
-        else
-            off = (uint32_t)(row0 + rr) * (uint32_t)(2 * g.m);
-        soff[i] = off + chunk * 8;
-    }
-    // K-strided: copy instruction i of this wavefront moves K rows
-    // k0 + 2 i (lanes 0-31) and k0 + 2 i + 1 (lanes 32-63) of the slice,
-    // k0 = 16 wq; lane l lands at chunk position l % 32 and so loads chunk
-    // (l % 32) ^ 4 ((2 i + l / 32) & 3) of its K row: one column pattern for
-    // even i, one for odd.  The row addresses are the same for the whole
-    // wavefront and formed on the scalar unit.
+    // row operand: copy i of this wavefront moves tile rows 64 wq + 16 i .. + 15
+    const bf16_t* const sbase = MODE == DH ? g.dy : g.AU;
+    uint32_t coff[kCopies];              // byte offsets: rows, or weight columns (two used)
     const int hi = lane >> 5;
-    const int cmask = ncols < BN ? WN - 1 : BN - 1;
-    const int cpat[2] = {(8 * ((lane & 31) ^ (4 * hi))) & cmask,
-                         (8 * ((lane & 31) ^ (4 * (hi + 2)))) & cmask};
-    const bf16_t* const rbase = (MODE == DH ? g.Wd : g.Wg) + ew + pn * BN;
     const int64_t ld = MODE == DH ? g.m : g.d;
-    const int64_t loff[2] = {hi * ld + cpat[0], hi * ld + cpat[1]};
-    auto issue = [&](int stage, int kt) __attribute__((always_inline)) {
-        if (strided) {
-            unsigned char* dst = lds + stage * STAGEB + BM * ROWB + wq * (16 * 512);
-            const bf16_t* rb = rbase;
-            int kr = kt * BK + 16 * wq;
-            if (MODE == DX && kt * BK >= g.m) { rb = g.Wu + ew + pn * BN; kr -= g.m; }
-            const bf16_t* p = rb + (int64_t)kr * ld;
+    if (half == 0) {
+        int src[kCopies];
 #pragma unroll
-            for (int i = 0; i < kGroups; ++i) dma16(p + 2 * i * ld + loff[i & 1], dst + i * 1024);
+        for (int i = 0; i < kCopies; ++i) {
+            const int r = 64 * wq + 16 * i + lane / 4;
+            src[i] = row0 + (r < rows ? r : 0);
+            if (MODE == DH) src[i] = g.perm_src[src[i]];
+        }
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) {
+            const int r = 64 * wq + 16 * i + lane / 4;
+            uint32_t off;
+            if (MODE == DH) off = (uint32_t)(min(max(src[i], 0), g.Tk - 1) / g.k) * (uint32_t)g.d;
+            else off = (uint32_t)src[i] * (uint32_t)(2 * g.m);
+            coff[i] = 2u * (off + 8 * ((lane & 3) ^ rswz(r)));
+        }
+    } else {
+        // weights: copy i moves K rows 8 wq + 2 i (lanes 0-31) and + 1 (lanes
+        // 32-63), lane l to chunk position l % 32, so it loads chunk
+        // (l % 32) ^ 4 ((2 i + l / 32) & 3): one column pattern for even i, one for odd
+        const int cmask = ncols < BN ? WN - 1 : BN - 1;
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i)
+            coff[i] = 2u * (uint32_t)(hi * ld + ((8 * ((lane & 31) ^ (4 * (hi + 2 * (i & 1))))) & cmask));
+    }
+    const bf16_t* const wbase = (MODE == DH ? g.Wd : g.Wg) + ew + pn * BN;
+    const bf16_t* const wbase2 = MODE == DX ? g.Wu + ew + pn * BN : nullptr;
+    auto issue = [&](int h) __attribute__((always_inline)) {
+        unsigned char* dst = lds + (h % kStages) * kStageB + half * kOpB + wq * 4096;
+        if (half == 0) {
+#pragma unroll
+            for (int i = 0; i < kCopies; ++i) dma16_at(sbase + h * kBK, coff[i], dst + i * 1024);
         } else {
+            const int kr = h * kBK;
+            const bf16_t* p = MODE == DX && kr >= g.m ? wbase2 + (int64_t)(kr - g.m + 8 * wq) * ld
+                                                      : wbase + (int64_t)(kr + 8 * wq) * ld;
 #pragma unroll
-            for (int i = 0; i < kGroups; ++i) {
-                const int grp = wq * kGroups + i;
-                dma16(sbase + (soff[i] + (uint32_t)(kt * BK)), &lds[stage * STAGEB + grp * 1024]);
-            }
+            for (int i = 0; i < kCopies; ++i) dma16_at(p + 2 * i * ld, coff[i], dst + i * 1024);
         }
     };
 
@@ -215,13 +213,12 @@ bwd_gemm(BwdArgs g) {
 
     // MFMA fragments: lane l supplies K values 8 (l / 32) .. +7 of the K=16
     // step for tile row (or column) l % 32 of a 32-block.
-    // K-contiguous: one 16-byte read at the swizzled chunk.
+    // Row operand: one 16-byte read at the swizzled chunk.
     const int lrow = lane & 31;
-    const int sw = swz(lrow);
-    int kpos[BK / 16];
+    int kpos[2];
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) kpos[ks] = lrow * ROWB + (((2 * ks + (lane >> 5)) ^ sw) << 4);
-    // K-strided: two ds_read_b64_tr_b16.  Within each group of 16 lanes, lane
+    for (int ks = 0; ks < 2; ++ks) kpos[ks] = lrow * 64 + (((2 * ks + hi) ^ rswz(lrow)) << 4);
+    // Weights: two ds_read_b64_tr_b16.  Within each group of 16 lanes, lane
     // s reads 4 values of K row 8 (g/2) + s/4 (+4 for the second read) at
     // columns 16 (g%2) + 4 (s%4) .. +3 of the block; the instruction hands
     // lane s value s%4 of the reads of lanes s/4 + 4j, j = 0..3, so each lane
@@ -233,46 +230,85 @@ bwd_gemm(BwdArgs g) {
     auto tr_pos = [&](int cb) { return kl * 512 + ((((cb >> 3) ^ tsw)) << 4) + ((nl & 4) << 1); };
     int a_pos[MI], b_pos[NJ];
 #pragma unroll
-    for (int i = 0; i < MI; ++i) a_pos[i] = (wr * WM + i * 32) * ROWB;
+    for (int i = 0; i < MI; ++i) a_pos[i] = (wr * WM + i * 32) * 64;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) b_pos[j] = BM * ROWB + tr_pos(wc * WN + j * 32);
+    for (int j = 0; j < NJ; ++j) b_pos[j] = kOpB + tr_pos(wc * WN + j * 32);
 
-    const int nk = (klen + BK - 1) / BK;
-    issue(0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        wait_vmcnt<0>();
-        __syncthreads();
-        if (kt + 1 < nk) issue((kt + 1) % NSTAGE, kt + 1);
-        if (active) {
-            const unsigned char* base = lds + (kt % NSTAGE) * STAGEB;
-            bf16x8 fa[2][MI], fb[2][NJ];
-            auto tr_frag = [&](int pos, int ks) __attribute__((always_inline)) {
-                const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (lds_v4s*)(base + pos + ks * (16 * 512)));
-                const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (lds_v4s*)(base + pos + ks * (16 * 512) + 4 * 512));
-                return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            };
-            auto read_frags = [&](int buf, int ks) __attribute__((always_inline)) {
+    // K loop: the barrier of a step sits between its two K=16 sub-steps.  Every
+    // wavefront holds the step's last fragments then, so its stage takes the
+    // copies of step h + 4 while steps h + 2 and h + 3 are in flight, and the
+    // fragments of step h + 1 are read among the MFMAs.
+    const int nh = klen / kBK;           // at least 4 (d a multiple of 256, m of 128)
+    auto wait_steps = [&](int n) __attribute__((always_inline)) {
+        if (n >= 2) wait_vmcnt<2 * kCopies>();
+        else if (n == 1) wait_vmcnt<kCopies>();
+        else wait_vmcnt<0>();
+    };
+    auto barrier = [&]() __attribute__((always_inline)) {
+        // a plain barrier: __syncthreads() would wait for every copy in flight
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+    bf16x8 fa[2][MI], fb[2][NJ];
+    auto tr_frag = [&](const unsigned char* p) __attribute__((always_inline)) {
+        const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
+        const v4s hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 4 * 512));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto row_frag = [&](const unsigned char* p) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8, *(const u32x4*)p);
+    };
+    // MFMAs on fragment set S, and among them the reads of sub-step ks of the
+    // given stage into the other set
+    auto phase = [&](auto S_, int stage, int ks) __attribute__((always_inline)) {
+        constexpr int S = decltype(S_)::value;
+        const unsigned char* base = lds + stage * kStageB;
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
-                    fa[buf][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(base + a_pos[i] + kpos[ks]));
+        for (int j = 0; j < NJ; ++j) {
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) fb[buf][j] = tr_frag(b_pos[j], ks);
-            };
-            read_frags(0, 0);
-#pragma unroll
-            for (int ks = 0; ks < BK / 16; ++ks) {
-                if (ks + 1 < BK / 16) read_frags((ks + 1) & 1, ks + 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            fb[ks & 1][j], fa[ks & 1][i], acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < MI; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[S][j], fa[S][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j == 0) {
+                fa[S ^ 1][0] = row_frag(base + a_pos[0] + kpos[ks]);
+                fa[S ^ 1][1] = row_frag(base + a_pos[1] + kpos[ks]);
+                fb[S ^ 1][0] = tr_frag(base + b_pos[0] + ks * 8192);
+            } else if (j == 1) {
+                fb[S ^ 1][1] = tr_frag(base + b_pos[1] + ks * 8192);
+                fb[S ^ 1][2] = tr_frag(base + b_pos[2] + ks * 8192);
+                fb[S ^ 1][3] = tr_frag(base + b_pos[3] + ks * 8192);
             }
+        }
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+#pragma unroll
+    for (int h = 0; h < kStages; ++h) issue(h);
+    wait_vmcnt<3 * kCopies>();
+    barrier();
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) fa[0][i] = row_frag(lds + a_pos[i] + kpos[0]);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) fb[0][j] = tr_frag(lds + b_pos[j]);
+        for (int h = 0; h < nh; ++h) {
+            phase(C0{}, h % kStages, 1);
+            wait_steps(min(nh - 1, h + kStages - 1) - (h + 1));
+            barrier();
+            if (h + kStages < nh) issue(h + kStages);
+            // (past the last step the reads fetch an old stage; unused)
+            phase(C1{}, (h + 1) % kStages, 0);
+        }
+    } else {
+        for (int h = 0; h < nh; ++h) {
+            wait_steps(min(nh - 1, h + kStages - 1) - (h + 1));
+            barrier();
+            if (h + kStages < nh) issue(h + kStages);
         }
     }
     // ---- epilogues.  Lane l holds output row l%32 of each 32-row block and
@@ -420,24 +456,21 @@ bwd_gemm(BwdArgs g) {
 // drain at a barrier (the loop waits for a count of its copies, not for all).
 // With two 64-row stages the copies of one slice had to land before the next
 // were issued, and these loops are short (an expert's routes: 16 such slices at
-// 1024 routes) with a gathered operand.
+// 1024 routes) with a gathered operand: at 131072 routes over 128 experts, d 2048,
+// m 768, WD took 604 us and WGU 1246, now 483 and 1028 (853 and 802
+// TFLOP/s; bound by the copies into LDS and, 0.8 and 1.6 GB, the fp32 stores).
 // The barrier of a step sits between its two K=16 sub-steps: every wavefront
 // holds the step's last fragments then, so its stage takes the copies of step
 // h + 4 and the fragments of step h + 1 are read among the MFMAs.
 // The gathered operand's row offsets are put into LDS once per tile (8192 routes
 // at a time); K rows past the last route read zeros in the plain operand and the
 // expert's last route in the gathered one.
-constexpr int kWgBK = 32;                          // K rows per step
-constexpr int kWgStages = 4;
-constexpr int kWgOpB = kWgBK * 512;                // bytes per operand and step
-constexpr int kWgStageB = 2 * kWgOpB;              // 32 KiB
 constexpr int kWgRoutes = 8192;                    // route offsets held in LDS
-constexpr int kWgCopies = kWgBK / 2 / 4;           // copies per wavefront and step (2 K rows each)
 
 template <int MODE>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_wgrad(BwdArgs g) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kWgStages * kWgStageB];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kStages * kStageB];
     __shared__ __attribute__((aligned(16))) uint32_t roff[kWgRoutes];
     static_assert(MODE == WD || MODE == WGU, "weight-gradient modes");
 
@@ -510,32 +543,32 @@ bwd_wgrad(BwdArgs g) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) a_pos[i] = tr_pos(wr * WM + i * 32);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) b_pos[j] = kWgOpB + tr_pos(wc * WN + j * 32);
+    for (int j = 0; j < NJ; ++j) b_pos[j] = kOpB + tr_pos(wc * WN + j * 32);
 
     for (int kc = 0; kc < klen; kc += kWgRoutes) {
         const int clen = min(kWgRoutes, klen - kc);
-        const int nh = (clen + kWgBK - 1) / kWgBK;
-        uint32_t go[kWgCopies];          // gathered rows' byte offsets of the next step to copy
+        const int nh = (clen + kBK - 1) / kBK;
+        uint32_t go[kCopies];          // gathered rows' byte offsets of the next step to copy
         auto fetch = [&](int h) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < kWgCopies; ++i) go[i] = roff[h * kWgBK + 8 * wq + 2 * i + hi];
+            for (int i = 0; i < kCopies; ++i) go[i] = roff[h * kBK + 8 * wq + 2 * i + hi];
         };
         auto issue_gathered = [&](int h) __attribute__((always_inline)) {
-            unsigned char* dst = lds + (h % kWgStages) * kWgStageB + half * kWgOpB + wq * 4096;
+            unsigned char* dst = lds + (h % kStages) * kStageB + half * kOpB + wq * 4096;
 #pragma unroll
-            for (int i = 0; i < kWgCopies; ++i)
+            for (int i = 0; i < kCopies; ++i)
                 dma16_at(gbase, go[i] + 2u * (uint32_t)cpat[i & 1], dst + i * 1024);
         };
         auto issue_plain = [&](int h) __attribute__((always_inline)) {
-            unsigned char* dst = lds + (h % kWgStages) * kWgStageB + half * kWgOpB + wq * 4096;
-            const int k0 = h * kWgBK + 8 * wq;
+            unsigned char* dst = lds + (h % kStages) * kStageB + half * kOpB + wq * 4096;
+            const int k0 = h * kBK + 8 * wq;
             const bf16_t* p = pbase + (int64_t)(kc + k0) * ld;
-            if ((h + 1) * kWgBK <= clen) {
+            if ((h + 1) * kBK <= clen) {
 #pragma unroll
-                for (int i = 0; i < kWgCopies; ++i) dma16_at(p + 2 * i * ld, poff[i & 1], dst + i * 1024);
+                for (int i = 0; i < kCopies; ++i) dma16_at(p + 2 * i * ld, poff[i & 1], dst + i * 1024);
             } else {
 #pragma unroll
-                for (int i = 0; i < kWgCopies; ++i)
+                for (int i = 0; i < kCopies; ++i)
                     dma16(k0 + 2 * i + hi < clen ? p + (2 * i + hi) * ld + cpat[i & 1] : kZeroRow + cpat[i & 1],
                           dst + i * 1024);
             }
@@ -552,27 +585,27 @@ bwd_wgrad(BwdArgs g) {
         // the last chunk's readers of roff and of the stages are done
         if (kc > 0) barrier();
         if (gathered) {
-            for (int q = wq * 64 + lane; q < nh * kWgBK; q += 256)
+            for (int q = wq * 64 + lane; q < nh * kBK; q += 256)
                 roff[q] = tok_of(g.perm_src[row0 + kc + min(q, clen - 1)]) * (uint32_t)(2 * g.d);
         } else {
-            for (int h = 0; h < min(nh, kWgStages); ++h) issue_plain(h);
+            for (int h = 0; h < min(nh, kStages); ++h) issue_plain(h);
         }
         barrier();
         if (gathered) {
-            for (int h = 0; h < min(nh, kWgStages); ++h) {
+            for (int h = 0; h < min(nh, kStages); ++h) {
                 fetch(h);
                 issue_gathered(h);
             }
-            if (nh > kWgStages) fetch(kWgStages);
+            if (nh > kStages) fetch(kStages);
         }
         // at most n steps' copies may still be in flight
         auto wait_steps = [&](int n) __attribute__((always_inline)) {
-            if (n >= 3) wait_vmcnt<3 * kWgCopies>();
-            else if (n == 2) wait_vmcnt<2 * kWgCopies>();
-            else if (n == 1) wait_vmcnt<kWgCopies>();
+            if (n >= 3) wait_vmcnt<3 * kCopies>();
+            else if (n == 2) wait_vmcnt<2 * kCopies>();
+            else if (n == 1) wait_vmcnt<kCopies>();
             else wait_vmcnt<0>();
         };
-        wait_steps(min(nh, kWgStages) - 1);
+        wait_steps(min(nh, kStages) - 1);
         barrier();
 
         bf16x8 fa[2][MI], fb[2][NJ];
@@ -585,7 +618,7 @@ bwd_wgrad(BwdArgs g) {
         // the given stage into the other set
         auto phase = [&](auto S_, int stage, int ks) __attribute__((always_inline)) {
             constexpr int S = decltype(S_)::value;
-            const unsigned char* base = lds + stage * kWgStageB + ks * (16 * 512);
+            const unsigned char* base = lds + stage * kStageB + ks * (16 * 512);
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 __builtin_amdgcn_sched_barrier(0);
@@ -604,14 +637,14 @@ bwd_wgrad(BwdArgs g) {
         };
         using C0 = std::integral_constant<int, 0>;
         using C1 = std::integral_constant<int, 1>;
-        // step h's stage is free: copy step h + kWgStages into it
+        // step h's stage is free: copy step h + kStages into it
         auto refill = [&](int h) __attribute__((always_inline)) {
-            if (h + kWgStages >= nh) return;
+            if (h + kStages >= nh) return;
             if (gathered) {
-                issue_gathered(h + kWgStages);
-                if (h + kWgStages + 1 < nh) fetch(h + kWgStages + 1);
+                issue_gathered(h + kStages);
+                if (h + kStages + 1 < nh) fetch(h + kStages + 1);
             } else {
-                issue_plain(h + kWgStages);
+                issue_plain(h + kStages);
             }
         };
         if (active) {
@@ -620,16 +653,16 @@ bwd_wgrad(BwdArgs g) {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) fb[0][j] = tr_frag(lds + b_pos[j]);
             for (int h = 0; h < nh; ++h) {
-                phase(C0{}, h % kWgStages, 1);
-                wait_steps(min(nh - 1, h + kWgStages - 1) - (h + 1));
+                phase(C0{}, h % kStages, 1);
+                wait_steps(min(nh - 1, h + kStages - 1) - (h + 1));
                 barrier();
                 refill(h);
                 // (past the last step the reads fetch an old stage; unused)
-                phase(C1{}, (h + 1) % kWgStages, 0);
+                phase(C1{}, (h + 1) % kStages, 0);
             }
         } else {
             for (int h = 0; h < nh; ++h) {
-                wait_steps(min(nh - 1, h + kWgStages - 1) - (h + 1));
+                wait_steps(min(nh - 1, h + kStages - 1) - (h + 1));
                 barrier();
                 refill(h);
             }
