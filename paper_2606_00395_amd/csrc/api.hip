@@ -210,11 +210,12 @@ BwdWs bwd_ws_layout(const pr2_moe_desc& d, void* base) {
     b.rbpart = (float*)take(sizeof(float) * (size_t)b.fw.max_tiles);
     b.nchunk = 0;
     if (d.renorm == 0) {
-        b.nchunk = (int)((d.T + 1023) / 1024);
+        b.nchunk = literal_chunks(d);
+        const size_t most = (size_t)literal_chunks_max(d);
         b.plog = (float*)take(sizeof(float) * (size_t)d.T * d.N);
         b.dpf = (float*)take(sizeof(float) * (size_t)d.T * d.N);
-        b.lwpart = (float*)take(sizeof(float) * (size_t)b.nchunk * d.d * d.N);
-        b.lbpart = (float*)take(sizeof(float) * (size_t)b.nchunk * d.N);
+        b.lwpart = (float*)take(sizeof(float) * most * d.d * d.N);
+        b.lbpart = (float*)take(sizeof(float) * most * d.N);
     }
     b.bytes = off + 256;
     return b;

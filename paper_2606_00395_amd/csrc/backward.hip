@@ -24,6 +24,7 @@
 // The router weight gradient is a separate pass over the x rows.
 // Every gradient is written exactly once (no atomics): results are
 // deterministic and overwrite the outputs.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -1151,21 +1152,24 @@ literal_dp_kernel(const float* dgp, int np, const int* inv, const float* gate, c
     }
 }
 
-constexpr int kLitTok = 1024;      // tokens per dW_r partial
 constexpr int kLitTile = 64;       // dW_r partial tile: 64 rows of d x 64 logits
+constexpr int kLitStep = 32;       // tokens staged at a time
 
 // part[c][i][j] = sum over the tokens of chunk c (in order) of x[t][i] dpf[t][j];
 // dbpart[c][j] the same of dpf[t][j] (workgroups of the first row block).
-template <typename T>
+// VEC (bf16, d % 8 == 0, N % 4 == 0): 16-byte loads, the next step's issued
+// before this step's products, so a step does not wait for its loads (3001
+// tokens, d 2048, N 64: 232 -> 20 us, with the shorter chunks).
+template <typename T, bool VEC>
 __global__ void __launch_bounds__(256)
-literal_wgrad_partial_kernel(const T* x, const float* dpf, int64_t Ttot, int d, int N,
+literal_wgrad_partial_kernel(const T* x, const float* dpf, int64_t Ttot, int tok, int d, int N,
                              float* part, float* dbpart) {
-    __shared__ __attribute__((aligned(16))) float xs[32][kLitTile];
-    __shared__ __attribute__((aligned(16))) float ps[32][kLitTile];
+    __shared__ __attribute__((aligned(16))) float xs[kLitStep][kLitTile];
+    __shared__ __attribute__((aligned(16))) float ps[kLitStep][kLitTile];
     const int i0 = blockIdx.x * kLitTile, j0 = blockIdx.y * kLitTile;
     const int64_t c = blockIdx.z;
-    const int64_t t0 = c * kLitTok;
-    const int64_t t1 = t0 + kLitTok < Ttot ? t0 + kLitTok : Ttot;
+    const int64_t t0 = c * tok;
+    const int64_t t1 = t0 + tok < Ttot ? t0 + tok : Ttot;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     float acc[4][4];
 #pragma unroll
@@ -1173,16 +1177,42 @@ literal_wgrad_partial_kernel(const T* x, const float* dpf, int64_t Ttot, int d, 
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[u][v] = 0.0f;
     float db = 0.0f;
-    for (int64_t tb = t0; tb < t1; tb += 32) {
-        for (int e = threadIdx.x; e < 32 * kLitTile; e += 256) {
-            const int r = e / kLitTile, q = e % kLitTile;
-            const int64_t t = tb + r;
-            xs[r][q] = (t < t1 && i0 + q < d) ? Act<T>::to_f32(x[t * d + i0 + q]) : 0.0f;
-            ps[r][q] = (t < t1 && j0 + q < N) ? dpf[t * N + j0 + q] : 0.0f;
+    // this thread's 8 columns of one row of x, 4 logits of two rows of dpf
+    const int xr = threadIdx.x >> 3, xc = (threadIdx.x & 7) * 8;
+    const int pr = threadIdx.x >> 4, pc = (threadIdx.x & 15) * 4;
+    u32x4 xv;
+    f32x4 pv[2];
+    auto fetch = [&](int64_t tb) {
+        xv = u32x4{0u, 0u, 0u, 0u};
+        if (tb + xr < t1 && i0 + xc < d) xv = *(const u32x4*)((const bf16_t*)x + (tb + xr) * d + i0 + xc);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            pv[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            const int64_t t = tb + pr + 16 * h;
+            if (t < t1 && j0 + pc < N) pv[h] = *(const f32x4*)(dpf + t * N + j0 + pc);
+        }
+    };
+    if (VEC) fetch(t0);
+    for (int64_t tb = t0; tb < t1; tb += kLitStep) {
+        if (VEC) {
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+                *(f32x4*)&xs[xr][xc + 4 * w] = f32x4{bf_lo(xv[2 * w]), bf_hi(xv[2 * w]),
+                                                     bf_lo(xv[2 * w + 1]), bf_hi(xv[2 * w + 1])};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) *(f32x4*)&ps[pr + 16 * h][pc] = pv[h];
+        } else {
+            for (int e = threadIdx.x; e < kLitStep * kLitTile; e += 256) {
+                const int r = e / kLitTile, q = e % kLitTile;
+                const int64_t t = tb + r;
+                xs[r][q] = (t < t1 && i0 + q < d) ? Act<T>::to_f32(x[t * d + i0 + q]) : 0.0f;
+                ps[r][q] = (t < t1 && j0 + q < N) ? dpf[t * N + j0 + q] : 0.0f;
+            }
         }
         __syncthreads();
-#pragma unroll 4
-        for (int r = 0; r < 32; ++r) {
+        if (VEC && tb + kLitStep < t1) fetch(tb + kLitStep);
+#pragma unroll 8
+        for (int r = 0; r < kLitStep; ++r) {
             // 16-byte reads: four rows of x (a 16-lane broadcast) and four logits
             const f32x4 a = *(const f32x4*)&xs[r][ty * 4];
             const f32x4 b = *(const f32x4*)&ps[r][tx * 4];
@@ -1192,7 +1222,7 @@ literal_wgrad_partial_kernel(const T* x, const float* dpf, int64_t Ttot, int d, 
                 for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(a[u], b[v], acc[u][v]);
         }
         if (blockIdx.x == 0 && threadIdx.x < kLitTile)
-            for (int r = 0; r < 32; ++r) db += ps[r][threadIdx.x];
+            for (int r = 0; r < kLitStep; ++r) db += ps[r][threadIdx.x];
         __syncthreads();
     }
 #pragma unroll
@@ -1216,7 +1246,15 @@ literal_wgrad_reduce_kernel(const float* part, const float* dbpart, int nchunk, 
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n;
          q += (int64_t)gridDim.x * 256) {
         float s = 0.0f;
-        for (int c = 0; c < nchunk; ++c) s += part[(int64_t)c * n + q];
+        int c = 0;
+        for (; c + 8 <= nchunk; c += 8) {       // eight loads in flight, added in chunk order
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(c + u) * n + q];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; c < nchunk; ++c) s += part[(int64_t)c * n + q];
         dW_r[q] = s;
         if (db_r && q < N) {
             float b = 0.0f;
@@ -1289,21 +1327,25 @@ literal_dx_combine_kernel(const T* dxr, const int* inv, const float* dpf, const 
 
 // The same with four consecutive columns per thread (d % 4 == 0): each
 // broadcast LDS read of four logits feeds 64 FMAs; every output's sums run in
-// the same order as above, so the result is bitwise the same.
+// the same order as above, so the result is bitwise the same.  Four tokens per
+// workgroup: bound by the latency of the W_r and route-row loads, so many short
+// workgroups beat fewer that share each W_r row (16, 8, 4 tokens at d 2048: 72,
+// 55, 52 us at 3001 tokens with 64 experts, 283, 240, 245 us at 16384 with 128).
+constexpr int kLitDxTok4 = 4;
 template <typename T>
 __global__ void __launch_bounds__(256)
 literal_dx_combine4_kernel(const T* dxr, const int* inv, const float* dpf, const float* wrt,
                            int64_t Ttot, int k, int d, int N, T* dx) {
-    __shared__ __attribute__((aligned(16))) float ps[kLitDxTok][64];
-    const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
-    const int64_t t0 = (int64_t)blockIdx.y * kLitDxTok;
-    float racc[kLitDxTok][4];
+    __shared__ __attribute__((aligned(16))) float ps[kLitDxTok4][64];
+    const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
+    const int64_t t0 = (int64_t)blockIdx.x * kLitDxTok4;
+    float racc[kLitDxTok4][4];
 #pragma unroll
-    for (int r = 0; r < kLitDxTok; ++r)
+    for (int r = 0; r < kLitDxTok4; ++r)
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) racc[r][cc] = 0.0f;
     for (int j0 = 0; j0 < N; j0 += 64) {
-        for (int e = threadIdx.x; e < kLitDxTok * 64; e += 256) {
+        for (int e = threadIdx.x; e < kLitDxTok4 * 64; e += 256) {
             const int r = e / 64, q = e % 64;
             const int64_t t = t0 + r;
             ps[r][q] = (t < Ttot && j0 + q < N) ? dpf[t * N + j0 + q] : 0.0f;
@@ -1313,12 +1355,13 @@ literal_dx_combine4_kernel(const T* dxr, const int* inv, const float* dpf, const
             const float* wcol = wrt + (int64_t)j0 * d + c;
             const int jn = N - j0 < 64 ? N - j0 : 64;
             int q = 0;
+#pragma unroll 2
             for (; q + 4 <= jn; q += 4) {
                 f32x4 w[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) w[u] = *(const f32x4*)(wcol + (int64_t)(q + u) * d);
 #pragma unroll
-                for (int r = 0; r < kLitDxTok; ++r) {
+                for (int r = 0; r < kLitDxTok4; ++r) {
                     const f32x4 p = *(const f32x4*)&ps[r][q];
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
@@ -1330,7 +1373,7 @@ literal_dx_combine4_kernel(const T* dxr, const int* inv, const float* dpf, const
             for (; q < jn; ++q) {
                 const f32x4 w = *(const f32x4*)(wcol + (int64_t)q * d);
 #pragma unroll
-                for (int r = 0; r < kLitDxTok; ++r)
+                for (int r = 0; r < kLitDxTok4; ++r)
 #pragma unroll
                     for (int cc = 0; cc < 4; ++cc) racc[r][cc] = fmaf(ps[r][q], w[cc], racc[r][cc]);
             }
@@ -1338,20 +1381,51 @@ literal_dx_combine4_kernel(const T* dxr, const int* inv, const float* dpf, const
         __syncthreads();
     }
     if (c >= d) return;
+    // the route rows of four tokens are loaded eight slots at a time before any is
+    // added (in slot order): one row per round trip took most of the kernel's time
+    constexpr int kSlots = 8, kTok = 4;
+    typedef T v4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int r = 0; r < kLitDxTok; ++r) {
-        const int64_t t = t0 + r;
-        if (t >= Ttot) break;
-        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int s = 0; s < k; ++s) {
-            const int q = inv[t * k + s];
-            if (q < 0) continue;
-            const T* row = dxr + (int64_t)q * d + c;
+    for (int r0 = 0; r0 < kLitDxTok4; r0 += kTok) {
+        if (t0 + r0 >= Ttot) break;
+        float acc[kTok][4];
 #pragma unroll
-            for (int cc = 0; cc < 4; ++cc) acc[cc] += Act<T>::to_f32(row[cc]);
+        for (int u = 0; u < kTok; ++u)
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) acc[u][cc] = 0.0f;
+        for (int s0 = 0; s0 < k; s0 += kSlots) {
+            int q[kTok][kSlots];
+            v4 row[kTok][kSlots];
+#pragma unroll
+            for (int u = 0; u < kTok; ++u)
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s) {
+                    const int64_t t = t0 + r0 + u;
+                    q[u][s] = t < Ttot && s0 + s < k ? inv[t * k + s0 + s] : -1;
+                }
+#pragma unroll
+            for (int u = 0; u < kTok; ++u)
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s)
+                    row[u][s] = *(const v4*)(dxr + (int64_t)max(q[u][s], 0) * d + c);
+#pragma unroll
+            for (int u = 0; u < kTok; ++u)
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s) {
+                    if (q[u][s] < 0) continue;
+#pragma unroll
+                    for (int cc = 0; cc < 4; ++cc) acc[u][cc] += Act<T>::to_f32(row[u][s][cc]);
+                }
         }
 #pragma unroll
-        for (int cc = 0; cc < 4; ++cc) dx[t * d + c + cc] = Act<T>::from_f32(acc[cc] + racc[r][cc]);
+        for (int u = 0; u < kTok; ++u) {
+            const int64_t t = t0 + r0 + u;
+            if (t >= Ttot) break;
+            v4 o;
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) o[cc] = Act<T>::from_f32(acc[u][cc] + racc[r0 + u][cc]);
+            *(v4*)(dx + t * d + c) = o;
+        }
     }
 }
 
@@ -1411,6 +1485,28 @@ bool bwd_mfma_ok(const pr2_moe_desc& d) {
     // (route entries below 2^32 / k keep the multiply-high token division exact)
     return mfma_shape_ok(d) && d.m % WN == 0 && d.d % BN == 0 && Tk * 2 * d.m < lim &&
            Tk * (int64_t)d.k < ((int64_t)1 << 32);
+}
+
+// Tokens per dW_r partial of the paper-literal backward: as many chunks as give
+// about 1024 workgroups (four per CU), of 64 to 1024 tokens.  (1024-token chunks
+// at every size left 96 workgroups at 3001 tokens, d 2048, N 64: 232 us.)
+int literal_chunk_tokens(const pr2_moe_desc& d) {
+    const int64_t tiles = (int64_t)((d.d + kLitTile - 1) / kLitTile) * ((d.N + kLitTile - 1) / kLitTile);
+    const int64_t tok = ((d.T * tiles + 1023) / 1024 + kLitStep - 1) / kLitStep * kLitStep;
+    return (int)std::min<int64_t>(1024, std::max<int64_t>(64, tok));
+}
+
+int literal_chunks(const pr2_moe_desc& d) {
+    const int tok = literal_chunk_tokens(d);
+    return (int)((d.T + tok - 1) / tok);
+}
+
+// chunks never exceed this, and it does not decrease with T (literal_chunks does,
+// where the chunk length steps up): the workspace is sized by it
+int literal_chunks_max(const pr2_moe_desc& d) {
+    const int64_t tiles = (int64_t)((d.d + kLitTile - 1) / kLitTile) * ((d.N + kLitTile - 1) / kLitTile);
+    const int64_t most = std::min<int64_t>((d.T + 63) / 64, (1024 + tiles - 1) / tiles);
+    return (int)std::max<int64_t>(most, (d.T + 1023) / 1024);
 }
 
 int bwd_partials(const pr2_moe_desc& d) { return bwd_mfma_ok(d) ? d.m / 128 : d.m; }
@@ -1529,13 +1625,18 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
                 LaunchScope scope("bwd_router_wgrad_literal", ts);
                 dim3 grid((unsigned)((d.d + kLitTile - 1) / kLitTile),
                           (unsigned)((d.N + kLitTile - 1) / kLitTile), (unsigned)ws.nchunk);
-                if (bf)
-                    hipLaunchKernelGGL(literal_wgrad_partial_kernel<bf16_t>, grid, dim3(256), 0, ts,
-                                       (const bf16_t*)x, ws.dpf, d.T, d.d, d.N, ws.lwpart,
+                const int tok = literal_chunk_tokens(d);
+                if (bf && d.d % 8 == 0 && d.N % 4 == 0)
+                    hipLaunchKernelGGL((literal_wgrad_partial_kernel<bf16_t, true>), grid, dim3(256), 0,
+                                       ts, (const bf16_t*)x, ws.dpf, d.T, tok, d.d, d.N, ws.lwpart,
+                                       ws.lbpart);
+                else if (bf)
+                    hipLaunchKernelGGL((literal_wgrad_partial_kernel<bf16_t, false>), grid, dim3(256),
+                                       0, ts, (const bf16_t*)x, ws.dpf, d.T, tok, d.d, d.N, ws.lwpart,
                                        ws.lbpart);
                 else
-                    hipLaunchKernelGGL(literal_wgrad_partial_kernel<float>, grid, dim3(256), 0, ts,
-                                       (const float*)x, ws.dpf, d.T, d.d, d.N, ws.lwpart,
+                    hipLaunchKernelGGL((literal_wgrad_partial_kernel<float, false>), grid, dim3(256),
+                                       0, ts, (const float*)x, ws.dpf, d.T, tok, d.d, d.N, ws.lwpart,
                                        ws.lbpart);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
                 const int64_t n = (int64_t)d.d * d.N;
@@ -1548,8 +1649,8 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
             if ((e = launch_transpose_wr(ts)) != hipSuccess) return e;
             LaunchScope scope("bwd_dx_combine_literal", ts);
             if (d.d % 4 == 0) {
-                dim3 grid4((unsigned)((d.d + 1023) / 1024),
-                           (unsigned)((d.T + kLitDxTok - 1) / kLitDxTok));
+                dim3 grid4((unsigned)((d.T + kLitDxTok4 - 1) / kLitDxTok4),
+                           (unsigned)((d.d + 1023) / 1024));
                 if (bf)
                     hipLaunchKernelGGL(literal_dx_combine4_kernel<bf16_t>, grid4, dim3(256), 0, ts,
                                        (const bf16_t*)w.O, w.inv, ws.dpf, ws.wrt, d.T, d.k, d.d, d.N,

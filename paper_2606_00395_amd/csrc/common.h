@@ -123,7 +123,7 @@ struct BwdWs {
     // paper-literal weights (renorm = 0) only: the router gradient is dense over N
     float* plog;        // [T, N] current router logits
     float* dpf;         // [T, N] router-logit gradient
-    float* lwpart;      // [nchunk, d, N] dW_r partials per chunk of 1024 tokens
+    float* lwpart;      // [nchunk, d, N] dW_r partials per chunk of tokens
     float* lbpart;      // [nchunk, N] db_r partials
     int nchunk;
     int np;
@@ -257,6 +257,8 @@ hipError_t launch_predictor_zero(const pr2_moe_desc& d, float* kl_out, float* lo
 // backward.hip
 bool bwd_mfma_ok(const pr2_moe_desc& d);
 int bwd_partials(const pr2_moe_desc& d);    // partial gate-gradient sums per route
+int literal_chunks(const pr2_moe_desc& d);      // dW_r partials of the paper-literal backward
+int literal_chunks_max(const pr2_moe_desc& d);
 struct BwdGrads {
     void* dx;
     float* dW_r;

@@ -1,6 +1,8 @@
 """Replay backward with chosen numbers of routes per expert: the token-contracted
 weight gradients advance 32 routes a step through four LDS stages and hold 8192
-route offsets at a time, the row-tile products 256 rows a tile.
+route offsets at a time, the row-tile products 256 rows a tile.  The weights are the
+paper-literal ones, whose dense router gradient is summed over chunks of 64 tokens
+(96 at the largest case).
 
 Every expert's slice of each expert-weight gradient is held to the bar of
 tests/test_gpu_backward.py (Frobenius ratio <= 2e-2) by itself."""
@@ -16,7 +18,7 @@ STEPS = [0, 1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 160, 161, 255, 
 
 
 @pytest.mark.parametrize("counts,d,m", [(STEPS, 256, 256), (STEPS, 512, 384),
-                                        ([8193, 5, 8192], 256, 128)],
+                                        ([8193, 5, 8192, 0], 256, 128)],
                          ids=["steps", "steps_half_panel", "offset_chunks"])
 def test_route_counts(counts, d, m):
     T, N = sum(counts), len(counts)
