@@ -79,6 +79,7 @@ __device__ __forceinline__ void dma16_at(const void* base, uint32_t off, const u
 // ------------------------------------------------------------ limits -----
 constexpr int kMaxExperts = 1024;
 constexpr int kEntriesPerPermBlock = 512;   // (token, slot) entries per permutation block
+constexpr int kPermSmallEntries = 16384;     // at most this many: one-workgroup permutation
 constexpr int kTileM = 256;                 // rows per grouped-GEMM tile (tile list granularity)
 
 inline int perm_tokens_per_block(int k) {
@@ -220,6 +221,8 @@ hipError_t launch_route_diagnostics(const pr2_moe_desc& d, const void* x, const 
 // workspace (written by the replay-weight pass)
 hipError_t launch_permute(const pr2_moe_desc& d, const void* idx, int64_t ldi, const ReplayWs& ws,
                           hipStream_t s, bool counted = false);
+// whether the permutation takes its one-workgroup form (which counts by itself)
+bool perm_small_ok(const pr2_moe_desc& d);
 hipError_t launch_combine(const pr2_moe_desc& d, const ReplayWs& ws, void* y, hipStream_t s);
 // p[0..n) = 0 (one workgroup; for the few error words)
 hipError_t launch_zero_i32(int* p, int n, hipStream_t s);

@@ -296,6 +296,112 @@ perm_scatter_kernel(const void* idx, int idx_dtype, int64_t ldi, int64_t T, int 
     }
 }
 
+// The whole permutation of a small batch in one launch of one workgroup: what
+// costs at these sizes is the launches, not the work: at 2048 entries, 128
+// experts, 6 us against 5 + 11.5 + 9 for count, scan and scatter; at 16000, 20
+// against 27.  Beyond 16384 the one workgroup is the slower (34 us at 24000, where
+// the router kernel forms the counts and scan and scatter take 23).  Wavefront w owns the w-th
+// contiguous run of G groups of 64 entries, counts them per expert in its own LDS
+// row, the rows become its first position per expert, and it places its entries
+// group by group as perm_scatter_kernel does.  The sorted list is formed in LDS
+// (scattered 2-byte writes) and stored in order.  Same outputs as the three
+// launches, including the count of out-of-range ids.
+template <int G>
+__global__ void __launch_bounds__(kScanThreads)
+perm_small_kernel(const void* idx, int idx_dtype, int64_t ldi, int entries, int k, int N, int bm,
+                  int* offsets, int* tiles, int* tile_count, int* perm_src, int* inv, int* err) {
+    constexpr int kWaves = kScanThreads / 64;
+    extern __shared__ int dyn[];
+    int* hist = dyn;                                    // [kWaves][N]
+    uint16_t* sorted = (uint16_t*)(dyn + kWaves * N);   // [entries]
+    __shared__ int sh[kWaves + 1];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int q0 = wave * G * 64 + lane;
+    int id[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int q = q0 + g * 64;
+        const int t = q / k;
+        id[g] = q < entries ? load_id(idx, idx_dtype, t * ldi + (q - t * k)) : -1;
+    }
+    for (int i = tid; i < kWaves * N; i += kScanThreads) hist[i] = 0;
+    __syncthreads();
+    int* mine = hist + wave * N;
+    int bad = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const bool in = q0 + g * 64 < entries;
+        if (id[g] < 0 || id[g] >= N) {
+            bad += in;
+            id[g] = -1;
+        }
+        if (id[g] >= 0) atomicAdd(mine + id[g], 1);
+    }
+    for (int off = 32; off >= 1; off >>= 1) bad += __shfl_xor(bad, off, 64);
+    if (lane == 0 && bad) atomicAdd(err + ERR_BAD_ID, bad);
+    __syncthreads();
+    // expert e (thread e; N <= kMaxExperts == kScanThreads): the wavefronts'
+    // counts become first positions, the totals the expert offsets and tiles
+    int n_e = 0;
+    if (tid < N)
+        for (int w = 0; w < kWaves; ++w) n_e += hist[w * N + tid];
+    int total, ntot;
+    const int base = block_exclusive_scan(n_e, sh, &total);
+    const int ntile = (n_e + bm - 1) / bm;
+    const int tstart = block_exclusive_scan(ntile, sh, &ntot);
+    if (tid < N) {
+        int run = base;
+        for (int w = 0; w < kWaves; ++w) {
+            const int c = hist[w * N + tid];
+            hist[w * N + tid] = run;
+            run += c;
+        }
+        offsets[tid] = base;
+        for (int j = 0; j < ntile; ++j) {
+            const int rows = n_e - j * bm;
+            tiles[3 * (tstart + j) + 0] = tid;
+            tiles[3 * (tstart + j) + 1] = base + j * bm;
+            tiles[3 * (tstart + j) + 2] = rows < bm ? rows : bm;
+        }
+    }
+    if (tid == 0) {
+        offsets[N] = total;
+        *tile_count = ntot;
+    }
+    __syncthreads();
+    const int nbits = 32 - __clz(max(N - 1, 1));
+    const uint64_t lt = lane ? ((~0ull) >> (64 - lane)) : 0ull;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int q = q0 + g * 64;
+        const int e = id[g];
+        const bool valid = e >= 0;
+        uint64_t peers = __ballot(valid);
+        if (peers == 0) {
+            if (q < entries) inv[q] = -1;
+            continue;
+        }
+        for (int bit = 0; bit < nbits; ++bit) {
+            const uint64_t ones = __ballot(valid && ((e >> bit) & 1));
+            peers &= ((e >> bit) & 1) ? ones : ~ones;
+        }
+        int pos = -1;
+        if (valid) {
+            const int b = mine[e];
+            pos = b + __popcll(peers & lt);
+            sorted[pos] = (uint16_t)q;
+            // the highest lane of each peer group advances the expert's cursor
+            if ((peers >> lane) == 1ull) mine[e] = b + __popcll(peers);
+        }
+        if (q < entries) inv[q] = pos;
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    for (int i = tid; i < total; i += kScanThreads) perm_src[i] = sorted[i];
+}
+
 // bf16, d % 8 == 0: each thread owns 8 consecutive columns of kCombTok tokens
 // per iteration and issues the loads of kCombSlots route slots of each before
 // summing them, so up to kCombTok * kCombSlots 16-byte loads are in flight
@@ -378,8 +484,33 @@ combine_kernel(const T* O, const int* inv, int64_t ntok, int k, int d, T* y) {
 
 }  // namespace
 
+namespace {
+size_t perm_small_lds(const pr2_moe_desc& d) {
+    return sizeof(int) * (kScanThreads / 64) * (size_t)d.N + sizeof(uint16_t) * (size_t)(d.T * d.k);
+}
+}  // namespace
+
+bool perm_small_ok(const pr2_moe_desc& d) {
+    return d.T * (int64_t)d.k <= kPermSmallEntries;
+}
+
 hipError_t launch_permute(const pr2_moe_desc& d, const void* idx, int64_t ldi, const ReplayWs& ws,
                           hipStream_t s, bool counted) {
+    if (perm_small_ok(d)) {
+        const int entries = (int)(d.T * d.k);
+        LaunchScope scope("perm_small", s);
+        switch ((entries + kScanThreads - 1) / kScanThreads) {
+#define PR2_SMALL(g) hipLaunchKernelGGL(perm_small_kernel<g>, dim3(1), dim3(kScanThreads), perm_small_lds(d), s, idx, d.idx_dtype, ldi, entries, d.k, d.N, kTileM, ws.offsets, ws.tiles, ws.tile_count, ws.perm_src, ws.inv, ws.err); break;
+            case 1: PR2_SMALL(1)
+            case 2: PR2_SMALL(2)
+            case 3: case 4: PR2_SMALL(4)
+            case 5: case 6: case 7: case 8: PR2_SMALL(8)
+            case 9: case 10: case 11: case 12: case 13: case 14: case 15: case 16: PR2_SMALL(16)
+            default: return hipErrorInvalidValue;
+#undef PR2_SMALL
+        }
+        return hipGetLastError();
+    }
     const int tb = perm_tokens_per_block(d.k);
     const size_t sm = sizeof(int) * (size_t)d.N;
     if (!counted) {

@@ -1326,7 +1326,7 @@ hipError_t launch_route_predict(const pr2_moe_desc& d, const void* x, const floa
     // the fused MFMA kernel (not its split-K form) also forms the permutation's
     // counts when its 64-token tiles hold whole count blocks
     auto add_counts = [&](PredictOut& o) {
-        if (!counts || (splitk_ok && use_splitk(d)) ||
+        if (!counts || (splitk_ok && use_splitk(d)) || perm_small_ok(d) ||
             !(d.k == 8 || d.k == 16 || d.k == 32 || d.k == 64))
             return;
         o.counts = counts;
@@ -1418,7 +1418,7 @@ hipError_t launch_router_replay(const pr2_moe_desc& d, const void* x, const floa
 }  // namespace
 
 bool replay_counts_fused(const pr2_moe_desc& d) {
-    return router_mfma_ok(d, d.N) && !use_splitk(d) &&
+    return router_mfma_ok(d, d.N) && !use_splitk(d) && !perm_small_ok(d) &&
            (d.k == 8 || d.k == 16 || d.k == 32 || d.k == 64);
 }
 
