@@ -723,93 +723,6 @@ __global__ void __launch_bounds__(1024) expert_order_kernel(const int* offsets, 
     }
 }
 
-// ------------------------------------------------------------ generic ----
-// One thread per output element; any shape, bf16 or fp32.
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-dh_generic(const T* dy, const int* perm_src, int k, const T* Wd, const float* gate, int d, int m,
-           const int* tiles, const int* tile_count, const T* AUin, T* AU, T* Hg, float* dgp) {
-    const int tile = blockIdx.x;
-    if (tile >= *tile_count) return;
-    const int expert = tiles[3 * tile], row0 = tiles[3 * tile + 1], rows = tiles[3 * tile + 2];
-    const int r = threadIdx.x;
-    const int j = blockIdx.y;
-    if (r >= rows || j >= m) return;
-    const int64_t q = row0 + r;
-    const int src = perm_src[q];
-    const T* dyr = dy + (int64_t)(src / k) * d;
-    const T* w = Wd + (int64_t)expert * d * m + j;
-    float G = 0.0f;
-    for (int i = 0; i < d; ++i) G = fmaf(Act<T>::to_f32(dyr[i]), Act<T>::to_f32(w[(int64_t)i * m]), G);
-    const T* ain = AUin + q * 2 * m;
-    T* au = AU + q * 2 * m;
-    float da, du, hg, hG;
-    swiglu_bwd(Act<T>::to_f32(ain[j]), Act<T>::to_f32(ain[m + j]), G, gate[src],
-               sizeof(T) == 2, da, du, hg, hG);
-    au[j] = Act<T>::from_f32(da);
-    au[m + j] = Act<T>::from_f32(du);
-    Hg[q * m + j] = Act<T>::from_f32(hg);
-    dgp[q * m + j] = hG;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-dx_generic(const T* AU, const T* Wg, const T* Wu, int d, int m, const int* tiles,
-           const int* tile_count, T* dxr) {
-    const int tile = blockIdx.x;
-    if (tile >= *tile_count) return;
-    const int expert = tiles[3 * tile], row0 = tiles[3 * tile + 1], rows = tiles[3 * tile + 2];
-    const int r = threadIdx.x;
-    const int i = blockIdx.y;
-    if (r >= rows || i >= d) return;
-    const int64_t q = row0 + r;
-    const T* au = AU + q * 2 * m;
-    const T* wg = Wg + (int64_t)expert * m * d + i;
-    const T* wu = Wu + (int64_t)expert * m * d + i;
-    float acc = 0.0f;
-    for (int j = 0; j < m; ++j) {
-        acc = fmaf(Act<T>::to_f32(au[j]), Act<T>::to_f32(wg[(int64_t)j * d]), acc);
-        acc = fmaf(Act<T>::to_f32(au[m + j]), Act<T>::to_f32(wu[(int64_t)j * d]), acc);
-    }
-    dxr[q * d + i] = Act<T>::from_f32(acc);
-}
-
-// dW_down[e][i][j] = sum over expert e's routes of dy[t][i] * (g H)[q][j]
-template <typename T>
-__global__ void __launch_bounds__(256)
-wd_generic(const T* dy, const T* Hg, const int* perm_src, const int* offsets, int k, int d, int m,
-           float* dWd) {
-    const int e = blockIdx.x;
-    const int i = blockIdx.y;
-    const int q0 = offsets[e], q1 = offsets[e + 1];
-    for (int j = threadIdx.x; j < m; j += blockDim.x) {
-        float acc = 0.0f;
-        for (int q = q0; q < q1; ++q)
-            acc = fmaf(Act<T>::to_f32(dy[(int64_t)(perm_src[q] / k) * d + i]),
-                       Act<T>::to_f32(Hg[(int64_t)q * m + j]), acc);
-        dWd[((int64_t)e * d + i) * m + j] = acc;
-    }
-}
-
-// dW_gate[e][r][i] (r < m) / dW_up[e][r - m][i] = sum over routes of (da | du)[q][r] * x[t][i]
-template <typename T>
-__global__ void __launch_bounds__(256)
-wgu_generic(const T* x, const T* AU, const int* perm_src, const int* offsets, int k, int d, int m,
-            float* dWg, float* dWu) {
-    const int e = blockIdx.x;
-    const int r = blockIdx.y;
-    const int q0 = offsets[e], q1 = offsets[e + 1];
-    float* out = r < m ? dWg + ((int64_t)e * m + r) * d : dWu + ((int64_t)e * m + r - m) * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) {
-        float acc = 0.0f;
-        for (int q = q0; q < q1; ++q)
-            acc = fmaf(Act<T>::to_f32(AU[(int64_t)q * 2 * m + r]),
-                       Act<T>::to_f32(x[(int64_t)(perm_src[q] / k) * d + i]), acc);
-        out[i] = acc;
-    }
-}
-
 // ------------------------------------------------------------ router ----
 
 // W_r [d, N] -> [N, d]
@@ -1443,36 +1356,6 @@ hipError_t zero(float* p, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_generic_gemms(const pr2_moe_desc& d, const void* x, const void* Wg,
-                                const void* Wu, const void* dy, const BwdWs& ws,
-                                const BwdGrads& out, hipStream_t s) {
-    // the SwiGLU backward (dh_generic) has already run: AU holds da | du, H holds g H
-    const ReplayWs& w = ws.fw;
-    hipError_t e;
-    {
-        LaunchScope scope("bwd_dx_generic", s);
-        hipLaunchKernelGGL(dx_generic<T>, dim3((unsigned)w.max_tiles, (unsigned)d.d), dim3(256), 0,
-                           s, (const T*)ws.AU, (const T*)Wg, (const T*)Wu, d.d, d.m, w.tiles,
-                           w.tile_count, (T*)w.O);
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    {
-        LaunchScope scope("bwd_wd_generic", s);
-        hipLaunchKernelGGL(wd_generic<T>, dim3((unsigned)d.N, (unsigned)d.d), dim3(256), 0, s,
-                           (const T*)dy, (const T*)w.H, w.perm_src, w.offsets, d.k, d.d, d.m,
-                           out.dW_down);
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    LaunchScope scope("bwd_wgu_generic", s);
-    hipLaunchKernelGGL(wgu_generic<T>, dim3((unsigned)d.N, (unsigned)(2 * d.m)), dim3(256), 0, s,
-                       (const T*)x, (const T*)ws.AU, w.perm_src, w.offsets, d.k, d.d, d.m,
-                       out.dW_gate, out.dW_up);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 // The MFMA backward takes every width the MFMA forward takes (m % 128 == 0): an
@@ -1509,7 +1392,7 @@ int literal_chunks_max(const pr2_moe_desc& d) {
     return (int)std::max<int64_t>(most, (d.T + 1023) / 1024);
 }
 
-int bwd_partials(const pr2_moe_desc& d) { return bwd_mfma_ok(d) ? d.m / 128 : d.m; }
+int bwd_partials(const pr2_moe_desc& d) { return bwd_mfma_ok(d) ? d.m / 128 : tile_partials(d); }
 
 hipError_t launch_zero_grads(const pr2_moe_desc& d, const BwdGrads& out, hipStream_t s) {
     LaunchScope scope("bwd_zero_grads", s);
@@ -1570,19 +1453,7 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
         LaunchScope scope("bwd_dh_swiglu", s);
         hipLaunchKernelGGL(bwd_gemm<DH>, grid_for(w.max_tiles * g.ntn), dim3(kThreads), 0, s, g);
     } else {
-        LaunchScope scope("bwd_dh_generic", s);
-        if (bf)
-            hipLaunchKernelGGL(dh_generic<bf16_t>, dim3((unsigned)w.max_tiles, (unsigned)d.m),
-                               dim3(256), 0, s, (const bf16_t*)dy, w.perm_src, d.k,
-                               (const bf16_t*)W_down, gate, d.d, d.m, w.tiles, w.tile_count,
-                               au_in ? (const bf16_t*)au_in : (const bf16_t*)ws.AU,
-                               (bf16_t*)ws.AU, (bf16_t*)w.H, ws.dgp);
-        else
-            hipLaunchKernelGGL(dh_generic<float>, dim3((unsigned)w.max_tiles, (unsigned)d.m),
-                               dim3(256), 0, s, (const float*)dy, w.perm_src, d.k,
-                               (const float*)W_down, gate, d.d, d.m, w.tiles, w.tile_count,
-                               au_in ? (const float*)au_in : (const float*)ws.AU,
-                               (float*)ws.AU, (float*)w.H, ws.dgp);
+        if ((e = launch_tile_dh(d, dy, W_down, gate, ws, au_in, s)) != hipSuccess) return e;
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // router-logit gradients (needed by the router weight gradient below)
@@ -1741,8 +1612,8 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
         if ((e = hipGetLastError()) != hipSuccess) return e;
         return tail(s);
     }
-    e = bf ? launch_generic_gemms<bf16_t>(d, x, W_gate, W_up, dy, ws, out, s)
-           : launch_generic_gemms<float>(d, x, W_gate, W_up, dy, ws, out, s);
+    // the SwiGLU backward has already run: AU holds da | du, H holds g H
+    e = launch_tile_grads(d, x, W_gate, W_up, dy, ws, out, s);
     if (e != hipSuccess) return e;
     return tail(s);
 }

@@ -237,6 +237,15 @@ bool mfma_shape_ok(const pr2_moe_desc& d);
 hipError_t launch_preact(const pr2_moe_desc& d, const void* x, const void* W_gate,
                          const void* W_up, const ReplayWs& ws, void* AU, hipStream_t s);
 
+// tile.hip: the shapes without an MFMA kernel (fp32, odd d or m)
+int tile_partials(const pr2_moe_desc& d);   // partial gate-gradient sums per route
+// pre-activations a | u into AU and/or H into H (either may be null)
+hipError_t launch_tile_gate_up(const pr2_moe_desc& d, const void* x, const void* W_gate,
+                               const void* W_up, const ReplayWs& ws, void* AU, void* H,
+                               hipStream_t s);
+hipError_t launch_tile_down(const pr2_moe_desc& d, const void* W_down, const float* gate,
+                            const ReplayWs& ws, hipStream_t s);
+
 // predictor.hip
 struct PredLossWs {
     float* p_cur;       // [T, N] current router logits
@@ -276,5 +285,12 @@ hipError_t launch_replay_backward(const pr2_moe_desc& d, const void* x, const vo
                                   const float* gate, const BwdWs& ws, const BwdGrads& out,
                                   hipStream_t s, const void* au_in = nullptr);
 hipError_t launch_zero_grads(const pr2_moe_desc& d, const BwdGrads& out, hipStream_t s);
+
+// tile.hip
+hipError_t launch_tile_dh(const pr2_moe_desc& d, const void* dy, const void* W_down,
+                          const float* gate, const BwdWs& ws, const void* au_in, hipStream_t s);
+hipError_t launch_tile_grads(const pr2_moe_desc& d, const void* x, const void* W_gate,
+                             const void* W_up, const void* dy, const BwdWs& ws,
+                             const BwdGrads& out, hipStream_t s);
 
 }  // namespace pr2

@@ -47,7 +47,7 @@
 // time, double-buffered, with the same barrier placement.  Per output the sums
 // run in the same K order as the 256-row panel, so H is bitwise the same.
 //
-// Other shapes and the fp32 path use a plain one-thread-per-output kernel.
+// Other shapes and the fp32 path take the fp32-FMA tile kernels of tile.hip.
 #include <type_traits>
 
 #include "common.h"
@@ -474,73 +474,6 @@ grouped_gemm_mfma(MfmaArgs g) {
     }
 }
 
-// ---------------------------------------------------------------- generic --
-// pre-activations a = x W_gate^T, u = x W_up^T of each permuted row (backward recompute)
-template <typename T>
-__global__ void __launch_bounds__(256)
-preact_generic(const T* x, const int* perm_src, int k, const T* Wg, const T* Wu, int d, int m,
-               const int* tiles, const int* tile_count, T* AU) {
-    const int tile = blockIdx.x;
-    if (tile >= *tile_count) return;
-    const int expert = tiles[3 * tile], row0 = tiles[3 * tile + 1], rows = tiles[3 * tile + 2];
-    const int r = threadIdx.x;
-    const int col = blockIdx.y;
-    if (r >= rows || col >= m) return;
-    const int64_t tok = perm_src[row0 + r] / k;
-    const T* xr = x + tok * d;
-    const T* g = Wg + ((int64_t)expert * m + col) * d;
-    const T* u = Wu + ((int64_t)expert * m + col) * d;
-    float a = 0.0f, b = 0.0f;
-    for (int i = 0; i < d; ++i) {
-        float xv = Act<T>::to_f32(xr[i]);
-        a = fmaf(xv, Act<T>::to_f32(g[i]), a);
-        b = fmaf(xv, Act<T>::to_f32(u[i]), b);
-    }
-    T* o = AU + (int64_t)(row0 + r) * 2 * m;
-    o[col] = Act<T>::from_f32(a);
-    o[m + col] = Act<T>::from_f32(b);
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-gemm1_generic(const T* x, const int* perm_src, int k, const T* Wg, const T* Wu, int d, int m,
-              const int* tiles, const int* tile_count, T* H) {
-    const int tile = blockIdx.x;
-    if (tile >= *tile_count) return;
-    const int expert = tiles[3 * tile], row0 = tiles[3 * tile + 1], rows = tiles[3 * tile + 2];
-    const int r = threadIdx.x;
-    const int col = blockIdx.y;
-    if (r >= rows || col >= m) return;
-    const int64_t tok = perm_src[row0 + r] / k;
-    const T* xr = x + tok * d;
-    const T* g = Wg + ((int64_t)expert * m + col) * d;
-    const T* u = Wu + ((int64_t)expert * m + col) * d;
-    float a = 0.0f, b = 0.0f;
-    for (int i = 0; i < d; ++i) {
-        float xv = Act<T>::to_f32(xr[i]);
-        a = fmaf(xv, Act<T>::to_f32(g[i]), a);
-        b = fmaf(xv, Act<T>::to_f32(u[i]), b);
-    }
-    H[(int64_t)(row0 + r) * m + col] = Act<T>::from_f32(a / (1.0f + expf(-a)) * b);
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-gemm2_generic(const T* H, const int* perm_src, const float* gate, const T* Wd, int d, int m,
-              const int* tiles, const int* tile_count, T* O) {
-    const int tile = blockIdx.x;
-    if (tile >= *tile_count) return;
-    const int expert = tiles[3 * tile], row0 = tiles[3 * tile + 1], rows = tiles[3 * tile + 2];
-    const int r = threadIdx.x;
-    const int col = blockIdx.y;
-    if (r >= rows || col >= d) return;
-    const T* h = H + (int64_t)(row0 + r) * m;
-    const T* w = Wd + ((int64_t)expert * d + col) * m;
-    float a = 0.0f;
-    for (int i = 0; i < m; ++i) a = fmaf(Act<T>::to_f32(h[i]), Act<T>::to_f32(w[i]), a);
-    O[(int64_t)(row0 + r) * d + col] = Act<T>::from_f32(gate[perm_src[row0 + r]] * a);
-}
-
 // ------------------------------------------- GEMM1 with a 384-row panel --
 constexpr int BPW = 384;                          // panel rows
 constexpr int WNW = 192;                          // panel rows per wavefront (96 gate + 96 up)
@@ -812,41 +745,9 @@ hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void*
         }
         return hipGetLastError();
     }
-    static_assert(BM == 256, "generic kernels map one thread per tile row");
-    if (au_out) {
-        hipError_t e = launch_preact(d, x, W_gate, W_up, ws, au_out, s);
-        if (e != hipSuccess) return e;
-    }
-    dim3 grid1((unsigned)ws.max_tiles, (unsigned)d.m);
-    dim3 grid2((unsigned)ws.max_tiles, (unsigned)d.d);
-    if (d.act_dtype == PR2_BF16) {
-        {
-            LaunchScope scope("gemm1_generic", s);
-            hipLaunchKernelGGL(gemm1_generic<bf16_t>, grid1, dim3(256), 0, s, (const bf16_t*)x,
-                               ws.perm_src, d.k, (const bf16_t*)W_gate, (const bf16_t*)W_up, d.d,
-                               d.m, ws.tiles, ws.tile_count, (bf16_t*)ws.H);
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        LaunchScope scope("gemm2_generic", s);
-        hipLaunchKernelGGL(gemm2_generic<bf16_t>, grid2, dim3(256), 0, s, (const bf16_t*)ws.H,
-                           ws.perm_src, gate, (const bf16_t*)W_down, d.d, d.m, ws.tiles,
-                           ws.tile_count, (bf16_t*)ws.O);
-    } else {
-        {
-            LaunchScope scope("gemm1_generic", s);
-            hipLaunchKernelGGL(gemm1_generic<float>, grid1, dim3(256), 0, s, (const float*)x,
-                               ws.perm_src, d.k, (const float*)W_gate, (const float*)W_up, d.d,
-                               d.m, ws.tiles, ws.tile_count, (float*)ws.H);
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        LaunchScope scope("gemm2_generic", s);
-        hipLaunchKernelGGL(gemm2_generic<float>, grid2, dim3(256), 0, s, (const float*)ws.H,
-                           ws.perm_src, gate, (const float*)W_down, d.d, d.m, ws.tiles,
-                           ws.tile_count, (float*)ws.O);
-    }
-    return hipGetLastError();
+    hipError_t e = launch_tile_gate_up(d, x, W_gate, W_up, ws, au_out, ws.H, s);
+    if (e != hipSuccess) return e;
+    return launch_tile_down(d, W_down, gate, ws, s);
 }
 
 hipError_t launch_preact(const pr2_moe_desc& d, const void* x, const void* W_gate,
@@ -873,17 +774,7 @@ hipError_t launch_preact(const pr2_moe_desc& d, const void* x, const void* W_gat
         hipLaunchKernelGGL(grouped_gemm_mfma<2>, dim3((unsigned)grid), dim3(kGemmThreads), 0, s, g);
         return hipGetLastError();
     }
-    dim3 grid((unsigned)ws.max_tiles, (unsigned)d.m);
-    LaunchScope scope("bwd_preact_generic", s);
-    if (d.act_dtype == PR2_BF16)
-        hipLaunchKernelGGL(preact_generic<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)x,
-                           ws.perm_src, d.k, (const bf16_t*)W_gate, (const bf16_t*)W_up, d.d, d.m,
-                           ws.tiles, ws.tile_count, (bf16_t*)AU);
-    else
-        hipLaunchKernelGGL(preact_generic<float>, grid, dim3(256), 0, s, (const float*)x,
-                           ws.perm_src, d.k, (const float*)W_gate, (const float*)W_up, d.d, d.m,
-                           ws.tiles, ws.tile_count, (float*)AU);
-    return hipGetLastError();
+    return launch_tile_gate_up(d, x, W_gate, W_up, ws, AU, nullptr, s);
 }
 
 }  // namespace pr2

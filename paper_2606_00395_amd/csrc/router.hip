@@ -453,38 +453,103 @@ __device__ void replay_token(const float* row, int64_t t, int N, const ReplayOut
 }
 
 // ------------------------------------------------- fp64 vector-ALU path ----
+// Few columns (NC <= 64) and few tokens: 8 tokens per workgroup, one thread per
+// (token, 4 columns, part of K), the parts' fp64 sums added in order at the end.
+// The 32-token tile of project_tile leaves 8 workgroups at 256 tokens and, with 8
+// columns, 240 of its 256 threads idle (28 us for the replay weights of 256 tokens,
+// d 64, N 8).
+constexpr int kSmallTM = 8;
+constexpr int kSmallKB = 64;
+constexpr int kSmallNC = 64;
+constexpr int kSmallTokens = 4096;
+
 template <typename XT>
-__global__ void __launch_bounds__(kThreads)
-route_predict_kernel(ProjArgs a, PredictOut o) {
+__device__ void project_small(const ProjArgs& a, int64_t t0, float* xs, float* ws, double* red,
+                              float* lds_logits) {
+    const int tid = threadIdx.x;
+    const int cg = (a.NC + 3) / 4;                   // column groups of 4
+    const int per = kSmallTM * cg;                   // threads per part
+    const int parts = kThreads / per;                // >= 2 (NC <= 64)
+    const int part = tid / per, tt = tid % per / cg, c0 = tid % cg * 4;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < a.d; k0 += kSmallKB) {
+        const int kn = min(kSmallKB, a.d - k0);
+        if (k0) __syncthreads();
+        for (int q = tid; q < kSmallTM * kSmallKB; q += kThreads) {
+            const int r = q / kSmallKB, kk = q % kSmallKB;
+            xs[r * (kSmallKB + 1) + kk] =
+                t0 + r < a.T && kk < kn ? Act<XT>::load((const XT*)a.x + (t0 + r) * a.d + k0 + kk) : 0.0f;
+        }
+        for (int q = tid; q < kn * a.NC; q += kThreads) {
+            const int kk = q / a.NC, c = q - kk * a.NC;
+            ws[kk * kSmallNC + c] = c < a.N ? a.W_r[(int64_t)(k0 + kk) * a.N + c]
+                                            : a.A[(int64_t)(k0 + kk) * a.r + (c - a.N)];
+        }
+        __syncthreads();
+        if (part < parts)
+            for (int kk = part; kk < kn; kk += parts) {
+                const double xv = (double)xs[tt * (kSmallKB + 1) + kk];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[j] = fma(xv, (double)ws[kk * kSmallNC + c0 + j], acc[j]);
+            }
+    }
+    if (part < parts)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) red[tid * 4 + j] = acc[j];
+    __syncthreads();
+    for (int q = tid; q < kSmallTM * a.NC; q += kThreads) {
+        const int r = q / a.NC, c = q - r * a.NC;
+        double s = 0.0;
+        for (int p = 0; p < parts; ++p) s += red[(p * per + r * cg + c / 4) * 4 + c % 4];
+        lds_logits[q] = (float)s;
+    }
+    __syncthreads();
+}
+
+// MAXV: 64-expert groups an epilogue lane may hold; SMALL: project_small (static
+// LDS), else project_tile (dynamic LDS)
+template <typename XT, int MAXV, bool SMALL, typename OUT, typename EPI>
+__device__ __forceinline__ void vector_router(const ProjArgs& a, const OUT& o, EPI epilogue) {
     extern __shared__ float smem[];
-    float* xs = smem;                                   // TM*KB
-    float* ws = xs + a.TM * a.KB;                       // KB*cols_per_pass
-    const int cols_per_pass = (kThreads / (a.TM / 4)) * 4;
-    float* lg = ws + a.KB * cols_per_pass;              // TM*NC
-    const int64_t t0 = (int64_t)blockIdx.x * a.TM;
-    project_tile<XT>(a, t0, xs, ws, lg);
-    for (int tt = threadIdx.x >> 6; tt < a.TM; tt += kThreads / 64) {
+    float* lg;
+    const int TM = SMALL ? kSmallTM : a.TM;
+    const int64_t t0 = (int64_t)blockIdx.x * TM;
+    if (SMALL) {
+        __shared__ float xs[kSmallTM * (kSmallKB + 1)];
+        // (4 columns of slack: the last column group may read past NC)
+        __shared__ float ws[kSmallKB * kSmallNC + 4];
+        __shared__ double red[kThreads * 4];
+        __shared__ float lgs[kSmallTM * kSmallNC];
+        lg = lgs;
+        project_small<XT>(a, t0, xs, ws, red, lg);
+    } else {
+        float* xs = smem;                                   // TM*KB
+        float* ws = xs + a.TM * a.KB;                       // KB*cols_per_pass
+        const int cols_per_pass = (kThreads / (a.TM / 4)) * 4;
+        lg = ws + a.KB * cols_per_pass;                     // TM*NC
+        project_tile<XT>(a, t0, xs, ws, lg);
+    }
+    for (int tt = threadIdx.x >> 6; tt < TM; tt += kThreads / 64) {
         const int64_t t = t0 + tt;
         if (t >= a.T) break;
-        predict_token<kMaxLanesVals>(lg + tt * a.NC, t, a.N, a.r, o, o.b_r);
+        epilogue(lg + tt * a.NC, t, o);
     }
 }
 
-template <typename XT>
+template <typename XT, int MAXV, bool SMALL>
+__global__ void __launch_bounds__(kThreads)
+route_predict_kernel(ProjArgs a, PredictOut o) {
+    vector_router<XT, MAXV, SMALL>(a, o, [&](const float* row, int64_t t, const PredictOut& po) {
+        predict_token<MAXV>(row, t, a.N, a.r, po, po.b_r);
+    });
+}
+
+template <typename XT, int MAXV, bool SMALL>
 __global__ void __launch_bounds__(kThreads)
 replay_gates_kernel(ProjArgs a, ReplayOut o) {
-    extern __shared__ float smem[];
-    float* xs = smem;
-    float* ws = xs + a.TM * a.KB;
-    const int cols_per_pass = (kThreads / (a.TM / 4)) * 4;
-    float* lg = ws + a.KB * cols_per_pass;
-    const int64_t t0 = (int64_t)blockIdx.x * a.TM;
-    project_tile<XT>(a, t0, xs, ws, lg);
-    for (int tt = threadIdx.x >> 6; tt < a.TM; tt += kThreads / 64) {
-        const int64_t t = t0 + tt;
-        if (t >= a.T) break;
-        replay_token<kMaxLanesVals>(lg + tt * a.NC, t, a.N, o, o.b_r, nullptr);
-    }
+    vector_router<XT, MAXV, SMALL>(a, o, [&](const float* row, int64_t t, const ReplayOut& ro) {
+        replay_token<MAXV>(row, t, a.N, ro, ro.b_r, nullptr);
+    });
 }
 
 // ------------------------------------------- 16-lane group epilogues ----
@@ -1226,6 +1291,10 @@ size_t router_smem(const ProjArgs& a) {
                             (size_t)a.TM * a.NC);
 }
 
+bool vector_small(const pr2_moe_desc& d, int NC) {
+    return NC <= kSmallNC && d.T <= kSmallTokens;
+}
+
 int ncp_of(int NC) { return ((NC + 63) / 64) * 64; }
 
 
@@ -1373,10 +1442,19 @@ hipError_t launch_route_predict(const pr2_moe_desc& d, const void* x, const floa
     dim3 grid((unsigned)((d.T + a.TM - 1) / a.TM));
     size_t smem = router_smem(a);
     LaunchScope scope("route_predict", s);
-    if (d.act_dtype == PR2_BF16)
-        hipLaunchKernelGGL(route_predict_kernel<bf16_t>, grid, dim3(kThreads), smem, s, a, o);
-    else
-        hipLaunchKernelGGL(route_predict_kernel<float>, grid, dim3(kThreads), smem, s, a, o);
+    const dim3 small((unsigned)((d.T + kSmallTM - 1) / kSmallTM));
+    if (vector_small(d, NC)) {
+        if (d.act_dtype == PR2_BF16)
+            hipLaunchKernelGGL((route_predict_kernel<bf16_t, 1, true>), small, dim3(kThreads), 0, s, a, o);
+        else
+            hipLaunchKernelGGL((route_predict_kernel<float, 1, true>), small, dim3(kThreads), 0, s, a, o);
+    } else if (d.act_dtype == PR2_BF16) {
+        hipLaunchKernelGGL((route_predict_kernel<bf16_t, kMaxLanesVals, false>), grid, dim3(kThreads),
+                           smem, s, a, o);
+    } else {
+        hipLaunchKernelGGL((route_predict_kernel<float, kMaxLanesVals, false>), grid, dim3(kThreads),
+                           smem, s, a, o);
+    }
     return hipGetLastError();
 }
 
@@ -1408,10 +1486,19 @@ hipError_t launch_router_replay(const pr2_moe_desc& d, const void* x, const floa
     dim3 grid((unsigned)((d.T + a.TM - 1) / a.TM));
     size_t smem = router_smem(a);
     LaunchScope scope(name, s);
-    if (d.act_dtype == PR2_BF16)
-        hipLaunchKernelGGL(replay_gates_kernel<bf16_t>, grid, dim3(kThreads), smem, s, a, o);
-    else
-        hipLaunchKernelGGL(replay_gates_kernel<float>, grid, dim3(kThreads), smem, s, a, o);
+    const dim3 small((unsigned)((d.T + kSmallTM - 1) / kSmallTM));
+    if (vector_small(d, d.N)) {
+        if (d.act_dtype == PR2_BF16)
+            hipLaunchKernelGGL((replay_gates_kernel<bf16_t, 1, true>), small, dim3(kThreads), 0, s, a, o);
+        else
+            hipLaunchKernelGGL((replay_gates_kernel<float, 1, true>), small, dim3(kThreads), 0, s, a, o);
+    } else if (d.act_dtype == PR2_BF16) {
+        hipLaunchKernelGGL((replay_gates_kernel<bf16_t, kMaxLanesVals, false>), grid, dim3(kThreads),
+                           smem, s, a, o);
+    } else {
+        hipLaunchKernelGGL((replay_gates_kernel<float, kMaxLanesVals, false>), grid, dim3(kThreads),
+                           smem, s, a, o);
+    }
     return hipGetLastError();
 }
 
