@@ -884,7 +884,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // per thread.
 __global__ void __launch_bounds__(256)
 router_split_kernel(const float* W_r, const float* A, const float* B, int N, int r, int folded,
-                    int NCp, bf16_t* Ws) {
+                    int NCp, bf16_t* Ws, unsigned long long* hist, int nhist) {
+    // the deviation histogram that the kernel after this one adds to
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int i = threadIdx.x; i < nhist; i += 256) hist[i] = 0ull;
     __shared__ bf16_t tile[3][32][kRBK + 1];
     // the predictor factors this workgroup folds in: A rows kt*32.. and B columns c0..
     constexpr int kStageR = 64;
@@ -1353,12 +1356,13 @@ hipError_t launch_router_mfma(const pr2_moe_desc& d, int NC, int r, const void* 
 }
 
 hipError_t launch_split(const float* W_r, const float* A, const float* B, const pr2_moe_desc& d,
-                        int r, int folded, bf16_t* Ws, hipStream_t s) {
+                        int r, int folded, bf16_t* Ws, hipStream_t s,
+                        unsigned long long* hist = nullptr) {
     const int NC = folded ? d.N : d.N + r;
     const int NCp = ncp_of(NC);
     LaunchScope scope("router_split", s);
     hipLaunchKernelGGL(router_split_kernel, dim3((unsigned)(NCp / 32), (unsigned)(d.d / kRBK)),
-                       dim3(256), 0, s, W_r, A, B, d.N, r, folded, NCp, Ws);
+                       dim3(256), 0, s, W_r, A, B, d.N, r, folded, NCp, Ws, hist, hist ? d.k + 1 : 0);
     return hipGetLastError();
 }
 
@@ -1464,14 +1468,26 @@ __global__ void __launch_bounds__(64) zero_u64_kernel(unsigned long long* p, int
     for (int i = threadIdx.x; i < n; i += 64) p[i] = 0ull;
 }
 
+hipError_t launch_zero_hist(unsigned long long* hist, int n, hipStream_t s) {
+    LaunchScope scope("route_diagnostics_zero", s);
+    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, hist, n);
+    return hipGetLastError();
+}
+
+// o.diag.hist (or null) is zeroed first: by the split kernel, or by a launch of its
+// own where there is no split (that launch took 4.5 of 58 us at 16384 tokens)
 hipError_t launch_router_replay(const pr2_moe_desc& d, const void* x, const float* W_r,
                                 const ReplayOut& o, void* split_ws, const char* name,
                                 hipStream_t s) {
     if (router_mfma_ok(d, d.N)) {
-        hipError_t e = launch_split(W_r, nullptr, nullptr, d, 0, 0, (bf16_t*)split_ws, s);
+        hipError_t e = launch_split(W_r, nullptr, nullptr, d, 0, 0, (bf16_t*)split_ws, s, o.diag.hist);
         if (e != hipSuccess) return e;
         LaunchScope scope(name, s);
         return launch_router_mfma<1>(d, d.N, 0, x, (const bf16_t*)split_ws, PredictOut{}, o, s);
+    }
+    if (o.diag.hist) {
+        hipError_t e = launch_zero_hist(o.diag.hist, d.k + 1, s);
+        if (e != hipSuccess) return e;
     }
     ProjArgs a;
     a.x = x;
@@ -1519,12 +1535,6 @@ hipError_t launch_replay_gates(const pr2_moe_desc& d, const void* x, const void*
         // the diagnostics epilogue runs on the same logits, before the weights
         g = DiagOut{diag->z_ref, diag->cur_idx, diag->overlap, diag->kl, diag->hist,
                     diag->p_out};
-        if (diag->hist) {
-            LaunchScope scope("replay_diagnostics_zero", s);
-            hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, diag->hist, d.k + 1);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
     }
     ReplayOut o{b_r, d.k, d.renorm, idx, d.idx_dtype, ldi, gate_out, err,
                 (v && v[0] == '1') ? 1 : 0, g, nullptr, 0, 0};
@@ -1549,13 +1559,7 @@ hipError_t launch_route_diagnostics(const pr2_moe_desc& d, const void* x, const 
                                     int64_t ldi, const float* W_r, const float* b_r,
                                     const float* z_ref, void* cur_idx, int* overlap, float* kl,
                                     unsigned long long* hist, void* split_ws, hipStream_t s) {
-    if (hist) {
-        LaunchScope scope("route_diagnostics_zero", s);
-        hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, hist, d.k + 1);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (d.T == 0) return hipSuccess;
+    if (d.T == 0) return hist ? launch_zero_hist(hist, d.k + 1, s) : hipSuccess;
     ReplayOut o{b_r, d.k, 1, idx, d.idx_dtype, ldi, nullptr, nullptr, 0,
                 DiagOut{z_ref, cur_idx, overlap, kl, hist, nullptr}, nullptr, 0, 0};
     return launch_router_replay(d, x, W_r, o, split_ws, "route_diagnostics", s);
