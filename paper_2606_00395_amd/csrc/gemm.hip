@@ -674,6 +674,137 @@ gemm1_wide(MfmaArgs g) {
     }
 }
 
+// --------------------------------------------- few rows per expert (decode) --
+// With a few routes per expert both GEMMs stream the experts' weights, and what
+// matters is bytes in flight.  The tiles above wait for all of a slice's copies at
+// its barrier; here a workgroup of four wavefronts takes 64 token rows x 128 panel
+// rows (GEMM1: 64 gate rows and the matching 64 up rows) through a ring of three
+// 64-K stages, two slices in flight, and two workgroups share a CU (72 KiB of LDS
+// each), so copies never stop.  Token rows past 64 are the next blockIdx.z (the
+// weights come from L2 then).  Sums run in the K order of the tiles above, so the
+// results are bitwise theirs.
+constexpr int kFewM = 64;           // token rows per workgroup
+constexpr int kFewP = 128;          // panel rows
+constexpr int kFewStageB = (kFewM + kFewP) * ROWB;      // 24 KiB
+constexpr int kFewStages = 3;
+
+template <int MODE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+few_rows_gemm(MfmaArgs g) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kFewStages * kFewStageB];
+    const int tile = blockIdx.y;
+    if (tile >= *g.tile_count) return;
+    const int expert = __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 0]);
+    const int row0 = __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 1]) + blockIdx.z * kFewM;
+    const int rows = min(kFewM, __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 2]) - (int)blockIdx.z * kFewM);
+    if (rows <= 0) return;
+    const int pn = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    // copies: panel rows 32 wave .. + 31 (four of 8 rows), token rows 16 wave .. + 15
+    // (two, fewer past the tile's end).  Panel row p < 64: gate row 64 pn + p, else up
+    // row 64 pn + p - 64 (GEMM2: output row 128 pn + p).
+    const bf16_t* wb = (MODE == 0 && wave >= 2 ? g.W1 : g.W0) + (int64_t)expert * g.w_stride;
+    const int prow0 = MODE == 0 ? 64 * pn + 32 * (wave & 1) : 128 * pn + 32 * wave;
+    uint32_t woff[4], xoff[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 8 * i + lane / 8;
+        woff[i] = 2u * (uint32_t)((prow0 + r) * g.K + ((lane % 8) ^ swz(r)) * 8);
+    }
+    const int nx = max(0, min(2, (rows - 16 * wave + 7) / 8));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = 16 * wave + 8 * i + lane / 8;
+        const int q = row0 + min(r, rows - 1);
+        const int64_t row = MODE == 0 ? (int64_t)(min(max(g.perm_src[q], 0), g.Tk - 1) / g.k) : q;
+        xoff[i] = 2u * (uint32_t)(row * g.K + ((lane % 8) ^ swz(r)) * 8);
+    }
+    auto issue = [&](int s) __attribute__((always_inline)) {
+        unsigned char* st = lds + (s % kFewStages) * kFewStageB;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dma16_at(wb + s * BK, woff[i], st + (kFewM + 32 * wave + 8 * i) * ROWB);
+        if (nx > 0) dma16_at(g.A + s * BK, xoff[0], st + 16 * wave * ROWB);
+        if (nx > 1) dma16_at(g.A + s * BK, xoff[1], st + (16 * wave + 8) * ROWB);
+    };
+    // slice s has landed, the one after it may still be in flight
+    auto wait_one = [&]() __attribute__((always_inline)) {
+        if (nx == 2) wait_vmcnt<6>();
+        else if (nx == 1) wait_vmcnt<5>();
+        else wait_vmcnt<4>();
+    };
+    const int lrow = lane % 16, grp = lane / 16;
+    const int cperm = ((grp & 1) << 1) | (grp >> 1);
+    int kpos[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) kpos[ks] = lrow * ROWB + (((4 * ks + cperm) ^ swz(lrow)) << 4);
+    // this wavefront's two 16-row panel tiles: gate and up rows 16 wave (GEMM2:
+    // output rows 32 wave, + 16)
+    const int b0 = (kFewM + (MODE == 0 ? 16 : 32) * wave) * ROWB;
+    const int b1 = b0 + (MODE == 0 ? 64 : 16) * ROWB;
+    accv acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = accv{0.0f, 0.0f, 0.0f, 0.0f};
+    const int mi = (rows + 15) / 16;
+    const int nk = g.K / BK;             // at least 2
+    issue(0);
+    issue(1);
+    for (int s = 0; s < nk; ++s) {
+        if (s + 1 < nk) wait_one();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        if (s + 2 < nk) issue(s + 2);
+        const unsigned char* st = lds + (s % kFewStages) * kFewStageB;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const bf16x8 w0 = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + b0 + kpos[ks]));
+            const bf16x8 w1 = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + b1 + kpos[ks]));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (i >= mi) continue;
+                const bf16x8 x = __builtin_bit_cast(bf16x8, *(const u32x4*)(st + 16 * i * ROWB + kpos[ks]));
+                acc[i][0] = mfma_bf16(w0, x, acc[i][0]);
+                acc[i][1] = mfma_bf16(w1, x, acc[i][1]);
+            }
+        }
+    }
+    // lane l holds outputs 4 (l / 16) .. + 3 of token row l % 16
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 16 * i + lrow;
+        if (r >= rows) continue;
+        bf16_t* orow = g.out + ((int64_t)row0 + r) * g.n_out;
+        uint32_t o[2];
+        if (MODE == 0) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float h0 = silu_f(acc[i][0][2 * h]) * acc[i][1][2 * h];
+                const float h1 = silu_f(acc[i][0][2 * h + 1]) * acc[i][1][2 * h + 1];
+                o[h] = (uint32_t)f32_to_bf16(h0) | ((uint32_t)f32_to_bf16(h1) << 16);
+            }
+            *(uint2*)(orow + 64 * pn + 16 * wave + 4 * grp) = make_uint2(o[0], o[1]);
+        } else {
+            const float gw = g.gate[min(max(g.perm_src[row0 + r], 0), g.Tk - 1)];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    o[h] = (uint32_t)f32_to_bf16(gw * acc[i][j][2 * h]) |
+                           ((uint32_t)f32_to_bf16(gw * acc[i][j][2 * h + 1]) << 16);
+                *(uint2*)(orow + 128 * pn + 32 * wave + 16 * j + 4 * grp) = make_uint2(o[0], o[1]);
+            }
+        }
+    }
+}
+
 }  // namespace
 
 bool mfma_shape_ok(const pr2_moe_desc& d) {
@@ -683,6 +814,16 @@ bool mfma_shape_ok(const pr2_moe_desc& d) {
     return d.act_dtype == PR2_BF16 && d.d % BP == 0 && d.m % 128 == 0 && d.d % BK == 0 &&
            d.m % BK == 0 && d.T * (int64_t)d.d < lim && Tk * d.m < lim &&
            (int64_t)d.m * d.d < lim;
+}
+
+// The few-rows kernels are taken up to this many routes per expert on average,
+// where they stop being the faster ones (us, tile kernel against few rows, 128 experts,
+// d 2048, m 768): GEMM1 41 | 15 at 0.06 routes per expert, 137 | 122 at 2, 148 | 138
+// at 4, 170 | 166 at 8, 156 | 155 at 16, 182 | 192 at 32; GEMM2 13 | 8, 82 | 63, 88 | 70,
+// 90 | 76, 94 | 83, 98 | 91 at 32, 104 | 103 at 48.  Without the 384-row panel (64
+// experts, m 1024) GEMM1 takes 132 | 96 at 16 and 111 | 114 at 32.
+static bool few_rows_ok(const pr2_moe_desc& d, int routes_per_expert) {
+    return d.T * (int64_t)d.k <= (int64_t)routes_per_expert * d.N;
 }
 
 hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void* W_gate,
@@ -707,7 +848,12 @@ hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void*
         g1.group = kGroupGemm1;
         int64_t work = ws.max_tiles * g1.ntn;
         int64_t grid = ((work + kNumXcd - 1) / kNumXcd) * kNumXcd;
-        if (!au_out && d.m % (BPW / 2) == 0) {
+        if (!au_out && few_rows_ok(d, d.m % (BPW / 2) == 0 ? 8 : 16)) {
+            LaunchScope scope("gemm1_few_rows", s);
+            hipLaunchKernelGGL(few_rows_gemm<0>,
+                               dim3((unsigned)(d.m / 64), (unsigned)ws.max_tiles, kTileM / kFewM),
+                               dim3(256), 0, s, g1);
+        } else if (!au_out && d.m % (BPW / 2) == 0) {
             // the 384-row panel: m / 192 panels per tile
             g1.ntn = d.m / (BPW / 2);
             const int64_t wide = ws.max_tiles * g1.ntn;
@@ -738,7 +884,12 @@ hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void*
         g2.group = kGroupGemm2;
         work = ws.max_tiles * g2.ntn;
         grid = ((work + kNumXcd - 1) / kNumXcd) * kNumXcd;
-        {
+        if (few_rows_ok(d, 32)) {
+            LaunchScope scope("gemm2_few_rows", s);
+            hipLaunchKernelGGL(few_rows_gemm<1>,
+                               dim3((unsigned)(d.d / kFewP), (unsigned)ws.max_tiles, kTileM / kFewM),
+                               dim3(256), 0, s, g2);
+        } else {
             LaunchScope scope("gemm2_down_scale", s);
             hipLaunchKernelGGL(grouped_gemm_mfma<1>, dim3((unsigned)grid), dim3(kGemmThreads), 0,
                                s, g2);
