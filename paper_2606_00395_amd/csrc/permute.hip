@@ -98,7 +98,7 @@ perm_scan_kernel(int* counts, int64_t nblk, int N, int bm, int* offsets, int* ti
     __shared__ int s_off[kMaxExperts + 1];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int kWaves = kScanThreads / 64;
     constexpr int kScanE = 8, kScanC = 8;
     int grand;
@@ -127,9 +127,11 @@ perm_scan_kernel(int* counts, int64_t nblk, int N, int bm, int* offsets, int* ti
             }
 #pragma unroll
             for (int c = 0; c < kScanC; ++c) {
+                v[i][c] = 0;
+                if (c >= P || e >= N) continue;         // uniform: no load at all
                 const int b = lane * P + c;
-                const bool ok = e < N && c < P && b < (int)nblk;
-                const int val = counts[ok ? (int64_t)e * nblk + b : 0];
+                const bool ok = b < (int)nblk;
+                const int val = counts[(int64_t)e * nblk + (ok ? b : 0)];
                 v[i][c] = ok ? val : 0;
             }
         }
