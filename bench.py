@@ -545,7 +545,7 @@ def run_backward(args, shape, dev):
     out["roofline"] = {"bound": "mfma", "kernel": dominant, "achieved": achieved, "peak": peak,
                        "unit": "TFLOP/s", "frac": achieved / peak,
                        "traffic": profiled_traffic(f"replay_backward_kernels_{shape.name}.txt",
-                                                   "bwd_gemm<3>")}
+                                                   "bwd_wgrad<3>")}
     out["kernels_ms"] = {n: round(v, 5) for n, v in kern.items()}
     out["mfma_frac"] = {n: f * unit / (kern[n] * 1e-3) / C.PEAK_BF16_FLOPS
                         for n, f in flops.items() if n in kern}
