@@ -76,10 +76,14 @@ struct BwdArgs {
     float* dWd;
 };
 
-// 16-byte chunk c of a 64-byte LDS row r sits at position c ^ rswz(r): the eight
-// rows of one cycle of a 16-byte fragment read, two neighbouring chunks each,
-// then hit distinct banks
-__device__ __forceinline__ int rswz(int r) { return (r >> 1) & 2; }
+// 16-byte chunk c of a 64-byte LDS row r sits at position c ^ rswz(r).  One pass of a
+// 16-byte fragment read serves lanes 0-3, 12-15, 20-23 and 24-27 together (the rest of
+// the half-wavefront in a second pass), that is, for rows equal mod 4, row / 4 of 0, 3,
+// 5, 6 (1, 2, 4, 7): (row / 4) % 4 gives each its own chunk position.  (Swizzled by bit
+// 2 of the row alone, those reads had 2-way conflicts, 0.76 cycles per LDS instruction
+// of the kernel: DH 601 -> 596 us, DX 886 -> 884 at 16384 tokens, 176 -> 173.5 and
+// 263.5 -> 261.6 at 3001.  The copies hide most of it.)
+__device__ __forceinline__ int rswz(int r) { return (r >> 2) & 3; }
 
 template <int n>
 __device__ __forceinline__ void wait_vmcnt() {
