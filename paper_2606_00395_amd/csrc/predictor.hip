@@ -157,6 +157,9 @@ hipError_t launch_prod(const TA* a, int64_t a_m, int64_t a_k, const TB* b, int64
 // about 226 clocks, made the token kernel 27 us instead of 20.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+// four floats of a tensor that is only promised to start at a 4-byte boundary (A); the
+// load is still one 16-byte instruction
+typedef f4 f4_unaligned __attribute__((aligned(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
 constexpr int kPTok = 8;            // tokens per workgroup, one wavefront each
@@ -238,7 +241,7 @@ __global__ void __launch_bounds__(64 * kPTok) pred_token_kernel(TokenArgs a) {
                 const float* p = a.A + (int64_t)(k0 + k) * r;
                 av[k] = f4{0.0f, 0.0f, 0.0f, 0.0f};
                 if (vec) {
-                    if (q0 < r) av[k] = *(const f4*)(p + q0);
+                    if (q0 < r) av[k] = *(const f4_unaligned*)(p + q0);
                 } else {
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
