@@ -26,6 +26,8 @@
 // by ballot, ids written ascending with their gates.  Replay: softmax over the
 // recorded ids (or over all N for the literal weights) from the current
 // router's logits.
+#include <type_traits>
+
 #include "common.h"
 
 namespace pr2 {
@@ -454,54 +456,96 @@ __device__ void replay_token(const float* row, int64_t t, int N, const ReplayOut
 
 // ------------------------------------------------- fp64 vector-ALU path ----
 // Few columns (NC <= 64) and few tokens: 8 tokens per workgroup, one thread per
-// (token, 4 columns, part of K), the parts' fp64 sums added in order at the end.
-// The 32-token tile of project_tile leaves 8 workgroups at 256 tokens and, with 8
-// columns, 240 of its 256 threads idle (28 us for the replay weights of 256 tokens,
-// d 64, N 8).
+// (token, column), two columns where there are more than 32.  Every logit is one
+// serial fp64 sum in K order, as project_tile's, so a token's logits do not depend on
+// the batch or on the columns beside them.  The 32-token tile of project_tile leaves
+// 8 workgroups at 256 tokens and, with 8 columns, 240 of its 256 threads idle (28 us
+// for the replay weights of 256 tokens, d 64, N 8).
 constexpr int kSmallTM = 8;
 constexpr int kSmallKB = 64;
 constexpr int kSmallNC = 64;
 constexpr int kSmallTokens = 4096;
 
 template <typename XT>
-__device__ void project_small(const ProjArgs& a, int64_t t0, float* xs, float* ws, double* red,
+__device__ void project_small(const ProjArgs& a, int64_t t0, float* xs, float* ws,
                               float* lds_logits) {
     const int tid = threadIdx.x;
-    const int cg = (a.NC + 3) / 4;                   // column groups of 4
-    const int per = kSmallTM * cg;                   // threads per part
-    const int parts = kThreads / per;                // >= 2 (NC <= 64)
-    const int part = tid / per, tt = tid % per / cg, c0 = tid % cg * 4;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const bool two = a.NC > 32;
+    const int per = two ? (a.NC + 1) / 2 : a.NC;     // threads per token, at most 32
+    const int tt = tid / per, c0 = tid % per, c1 = c0 + per;
+    const bool active = tt < kSmallTM;
+    // a K slice's elements of this thread, loaded while the slice before is summed: x
+    // by (token, K), the weights by (K, column) with the columns padded to 2^lg.  Past
+    // the last token, K value or column they repeat it: nothing stored sums those.
+    constexpr int kXN = kSmallTM * kSmallKB / kThreads, kWN = kSmallKB * kSmallNC / kThreads;
+    const int lg = a.NC > 1 ? 32 - __clz(a.NC - 1) : 0;
+    const int wk = tid >> lg, wc = tid & ((1 << lg) - 1), kstep = kThreads >> lg;
+    const int nw = max(1, kSmallKB / kstep);         // weights of this thread, at most kWN
+    const int cc = min(wc, a.NC - 1);
+    const float* wcol = cc < a.N ? a.W_r + cc : a.A + (cc - a.N);
+    const int ldw = cc < a.N ? a.N : a.r;
+    XT xn[kXN];
+    float wn[kWN];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < kXN; ++i) {
+            const int64_t t = min(t0 + (tid + i * kThreads) / kSmallKB, a.T - 1);
+            xn[i] = ((const XT*)a.x)[t * a.d + min(k0 + tid % kSmallKB, a.d - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < kWN; ++i)
+            if (i < nw) wn[i] = wcol[(int64_t)min(k0 + wk + i * kstep, a.d - 1) * ldw];
+    };
+    double acc0 = 0.0, acc1 = 0.0;
+    fetch(0);
     for (int k0 = 0; k0 < a.d; k0 += kSmallKB) {
         const int kn = min(kSmallKB, a.d - k0);
         if (k0) __syncthreads();
-        for (int q = tid; q < kSmallTM * kSmallKB; q += kThreads) {
-            const int r = q / kSmallKB, kk = q % kSmallKB;
-            xs[r * (kSmallKB + 1) + kk] =
-                t0 + r < a.T && kk < kn ? Act<XT>::load((const XT*)a.x + (t0 + r) * a.d + k0 + kk) : 0.0f;
-        }
-        for (int q = tid; q < kn * a.NC; q += kThreads) {
-            const int kk = q / a.NC, c = q - kk * a.NC;
-            ws[kk * kSmallNC + c] = c < a.N ? a.W_r[(int64_t)(k0 + kk) * a.N + c]
-                                            : a.A[(int64_t)(k0 + kk) * a.r + (c - a.N)];
-        }
+#pragma unroll
+        for (int i = 0; i < kXN; ++i)
+            xs[(tid + i * kThreads) / kSmallKB * (kSmallKB + 1) + tid % kSmallKB] = Act<XT>::to_f32(xn[i]);
+#pragma unroll
+        for (int i = 0; i < kWN; ++i)
+            if (i < nw && wk + i * kstep < kSmallKB) ws[(wk + i * kstep) * kSmallNC + wc] = wn[i];
         __syncthreads();
-        if (part < parts)
-            for (int kk = part; kk < kn; kk += parts) {
-                const double xv = (double)xs[tt * (kSmallKB + 1) + kk];
+        if (k0 + kSmallKB < a.d) fetch(k0 + kSmallKB);
+        if (active) {
+            const float* xr = xs + tt * (kSmallKB + 1);
+            const float* wr0 = ws + c0;
+            const float* wr1 = ws + c1;             // (c1 < 64)
+            // sixteen terms at a time, their LDS reads ahead of the sums (the compiler
+            // alone reads two terms at a time and waits for them), then the rest
+            constexpr int kU = 16;
+            int kk = 0;
+            auto sixteen = [&](auto two_) {
+                float xu[kU], w0[kU], w1[kU];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[j] = fma(xv, (double)ws[kk * kSmallNC + c0 + j], acc[j]);
+                for (int u = 0; u < kU; ++u) {
+                    xu[u] = xr[kk + u];
+                    w0[u] = wr0[(kk + u) * kSmallNC];
+                    if (decltype(two_)::value) w1[u] = wr1[(kk + u) * kSmallNC];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    acc0 = fma((double)xu[u], (double)w0[u], acc0);
+                    if (decltype(two_)::value) acc1 = fma((double)xu[u], (double)w1[u], acc1);
+                }
+            };
+            if (two) {
+                for (; kk + kU <= kn; kk += kU) sixteen(std::true_type{});
+            } else {
+                for (; kk + kU <= kn; kk += kU) sixteen(std::false_type{});
             }
+            for (; kk < kn; ++kk) {
+                acc0 = fma((double)xr[kk], (double)wr0[kk * kSmallNC], acc0);
+                if (two) acc1 = fma((double)xr[kk], (double)wr1[kk * kSmallNC], acc1);
+            }
+        }
     }
-    if (part < parts)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) red[tid * 4 + j] = acc[j];
-    __syncthreads();
-    for (int q = tid; q < kSmallTM * a.NC; q += kThreads) {
-        const int r = q / a.NC, c = q - r * a.NC;
-        double s = 0.0;
-        for (int p = 0; p < parts; ++p) s += red[(p * per + r * cg + c / 4) * 4 + c % 4];
-        lds_logits[q] = (float)s;
+    if (active) {
+        lds_logits[tt * a.NC + c0] = (float)acc0;
+        if (two && c1 < a.NC) lds_logits[tt * a.NC + c1] = (float)acc1;
     }
     __syncthreads();
 }
@@ -516,12 +560,10 @@ __device__ __forceinline__ void vector_router(const ProjArgs& a, const OUT& o, E
     const int64_t t0 = (int64_t)blockIdx.x * TM;
     if (SMALL) {
         __shared__ float xs[kSmallTM * (kSmallKB + 1)];
-        // (4 columns of slack: the last column group may read past NC)
-        __shared__ float ws[kSmallKB * kSmallNC + 4];
-        __shared__ double red[kThreads * 4];
+        __shared__ float ws[kSmallKB * kSmallNC];
         __shared__ float lgs[kSmallTM * kSmallNC];
         lg = lgs;
-        project_small<XT>(a, t0, xs, ws, red, lg);
+        project_small<XT>(a, t0, xs, ws, lg);
     } else {
         float* xs = smem;                                   // TM*KB
         float* ws = xs + a.TM * a.KB;                       // KB*cols_per_pass
