@@ -680,9 +680,20 @@ gemm1_wide(MfmaArgs g) {
 // its barrier; here a workgroup of four wavefronts takes 64 token rows x 128 panel
 // rows (GEMM1: 64 gate rows and the matching 64 up rows) through a ring of three
 // 64-K stages, two slices in flight, and two workgroups share a CU (72 KiB of LDS
-// each), so copies never stop.  Token rows past 64 are the next blockIdx.z (the
-// weights come from L2 then).  Sums run in the K order of the tiles above, so the
+// each), so copies never stop.  Token rows past 64 are the next blockIdx.y (the
+// weights are read again then).  Sums run in the K order of the tiles above, so the
 // results are bitwise theirs.
+//
+// Work order: XCD b % 8 takes a contiguous range of the (tile, panel) list.  With
+// the panels dealt round-robin over the XCDs, all resident workgroups (they walk K
+// nearly in step) read one contiguous stretch of weights, and where a row is a
+// multiple of 8 KiB their copies fell on few memory channels: a layer of 64 tokens,
+// d 4096, 64 experts, m 2048 took 664 us against 597 with the tiles, now 567; 128
+// experts, d 4096, m 1536 865 (859), now 813; m 4096, d 2048 649 (589), now 567.
+// Rows of other lengths: within 3 % (d 3840 538 -> 536).  The parts after the first,
+// which only busy experts have, are dealt round-robin, or an XCD whose range holds
+// several busy experts would finish last (512 tokens under a sorted Zipf load: 325 us
+// round-robin, 434 in ranges).
 constexpr int kFewM = 64;           // token rows per workgroup
 constexpr int kFewP = 128;          // panel rows
 constexpr int kFewStageB = (kFewM + kFewP) * ROWB;      // 24 KiB
@@ -692,13 +703,21 @@ template <int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 few_rows_gemm(MfmaArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kFewStages * kFewStageB];
-    const int tile = blockIdx.y;
-    if (tile >= *g.tile_count) return;
+    const int part = blockIdx.y;             // 64-row part of the tile
+    const int L = *g.tile_count * g.ntn;
+    int item = blockIdx.x;
+    if (part == 0) {                         // the XCD's range
+        const int per_xcd = (L + kNumXcd - 1) / kNumXcd;
+        const int local = blockIdx.x / kNumXcd;
+        if (local >= per_xcd) return;
+        item = (blockIdx.x % kNumXcd) * per_xcd + local;
+    }
+    if (item >= L) return;
+    const int tile = item / g.ntn, pn = item % g.ntn;
     const int expert = __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 0]);
-    const int row0 = __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 1]) + blockIdx.z * kFewM;
-    const int rows = min(kFewM, __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 2]) - (int)blockIdx.z * kFewM);
+    const int row0 = __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 1]) + part * kFewM;
+    const int rows = min(kFewM, __builtin_amdgcn_readfirstlane(g.tiles[3 * tile + 2]) - part * kFewM);
     if (rows <= 0) return;
-    const int pn = blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -816,14 +835,34 @@ bool mfma_shape_ok(const pr2_moe_desc& d) {
            (int64_t)d.m * d.d < lim;
 }
 
-// The few-rows kernels are taken up to this many routes per expert on average,
-// where they stop being the faster ones (us, tile kernel against few rows, 128 experts,
-// d 2048, m 768): GEMM1 41 | 15 at 0.06 routes per expert, 137 | 122 at 2, 148 | 138
-// at 4, 170 | 166 at 8, 156 | 155 at 16, 182 | 192 at 32; GEMM2 13 | 8, 82 | 63, 88 | 70,
-// 90 | 76, 94 | 83, 98 | 91 at 32, 104 | 103 at 48.  Without the 384-row panel (64
-// experts, m 1024) GEMM1 takes 132 | 96 at 16 and 111 | 114 at 32.
+// The few-rows kernels are taken up to this many routes per expert on average (GEMM1:
+// 8 where it would otherwise run the 384-row panel, else 16; GEMM2: 32), from replay
+// calls of one layer, both forms in turn on the same buffers, mean of six sets of
+// buffers (the tiles' time moves up to 15 % with where the weights lie).  Gain of the
+// few-rows form in us of the call under an even load | 8 experts e^3 times as busy
+// | a Zipf(1.1) load:
+//   d/N/m             routes     tiles             GEMM1               GEMM2
+//   2048/128/768          2   244  217  209     9   19   32         17   12   13
+//    (384-row panel)      8   265  259  256    11   -2    6         12    8   11
+//                        32   297  348  357                         11   10   10
+//   4096/128/1536         2   842  658  618    38    4   40         57   36   26
+//    (384-row panel)      8   901  899  838    19  -14   -5         39   28   37
+//                        32   913 1027 1071                         37   13    7
+//   2048/64/1024          8   198  191  194    11   11   11          6    6    6
+//                        16   192  207  208     8    0    0          6    1   -1
+//                        32   192  217  211                          6   -2   -1
+//   2048/64/1408         16   239  248  254    12   -1    9          8   -3   -2
+//                        32   255  280  286                          7   -2   10
+//   4096/64/2048          8   595  612  601    15   30   28         11   16   17
+//                        16   606  623  610    22  -20  -13          9  -13   -5
+//                        32   623  659  655                          8  -10   -7
+// The limits are where an uneven load begins to lose; an even one gains beyond them.
 static bool few_rows_ok(const pr2_moe_desc& d, int routes_per_expert) {
     return d.T * (int64_t)d.k <= (int64_t)routes_per_expert * d.N;
+}
+
+static dim3 few_rows_grid(int64_t items) {
+    return dim3((unsigned)((items + kNumXcd - 1) / kNumXcd * kNumXcd), kTileM / kFewM);
 }
 
 hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void* W_gate,
@@ -850,9 +889,8 @@ hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void*
         int64_t grid = ((work + kNumXcd - 1) / kNumXcd) * kNumXcd;
         if (!au_out && few_rows_ok(d, d.m % (BPW / 2) == 0 ? 8 : 16)) {
             LaunchScope scope("gemm1_few_rows", s);
-            hipLaunchKernelGGL(few_rows_gemm<0>,
-                               dim3((unsigned)(d.m / 64), (unsigned)ws.max_tiles, kTileM / kFewM),
-                               dim3(256), 0, s, g1);
+            g1.ntn = d.m / (kFewP / 2);
+            hipLaunchKernelGGL(few_rows_gemm<0>, few_rows_grid(ws.max_tiles * g1.ntn), dim3(256), 0, s, g1);
         } else if (!au_out && d.m % (BPW / 2) == 0) {
             // the 384-row panel: m / 192 panels per tile
             g1.ntn = d.m / (BPW / 2);
@@ -886,9 +924,8 @@ hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void*
         grid = ((work + kNumXcd - 1) / kNumXcd) * kNumXcd;
         if (few_rows_ok(d, 32)) {
             LaunchScope scope("gemm2_few_rows", s);
-            hipLaunchKernelGGL(few_rows_gemm<1>,
-                               dim3((unsigned)(d.d / kFewP), (unsigned)ws.max_tiles, kTileM / kFewM),
-                               dim3(256), 0, s, g2);
+            g2.ntn = d.d / kFewP;
+            hipLaunchKernelGGL(few_rows_gemm<1>, few_rows_grid(ws.max_tiles * g2.ntn), dim3(256), 0, s, g2);
         } else {
             LaunchScope scope("gemm2_down_scale", s);
             hipLaunchKernelGGL(grouped_gemm_mfma<1>, dim3((unsigned)grid), dim3(kGemmThreads), 0,

@@ -15,6 +15,9 @@ CASES = [
     (64, 1, 256, 128, 150, (1, 7, 8, 9, 15, 16, 17)),
     (128, 1, 512, 192, 400, (31, 32, 33, 48, 49, 63, 64, 65)),
     (256, 2, 256, 384, 300, (128, 129, 255, 256, 257)),
+    # fewer work items than XCDs, and ranges that the XCDs do not share evenly
+    (4, 1, 256, 128, 40, (1, 2, 39, 40)),
+    (13, 1, 768, 640, 100, (1, 65, 100)),
 ]
 
 
