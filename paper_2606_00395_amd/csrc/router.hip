@@ -455,16 +455,17 @@ __device__ void replay_token(const float* row, int64_t t, int N, const ReplayOut
 }
 
 // ------------------------------------------------- fp64 vector-ALU path ----
-// Few columns (NC <= 64) and few tokens: 8 tokens per workgroup, one thread per
-// (token, column), two columns where there are more than 32.  Every logit is one
-// serial fp64 sum in K order, as project_tile's, so a token's logits do not depend on
-// the batch or on the columns beside them.  The 32-token tile of project_tile leaves
-// 8 workgroups at 256 tokens and, with 8 columns, 240 of its 256 threads idle (28 us
-// for the replay weights of 256 tokens, d 64, N 8).
+// At most 64 columns: 8 tokens per workgroup, one thread per (token, column), two
+// columns where there are more than 32.  Every logit is one serial fp64 sum in K order,
+// as project_tile's, so a token's logits do not depend on the batch or on the columns
+// beside them.  The 32-token tile of project_tile leaves 8 workgroups at 256 tokens
+// and, with 8 columns, 240 of its 256 threads idle, and waits for each K slice's loads.
+// Route call, fp32, us, project_tile | this form: d 64, N 8: 46 | 10 at 256 and at 4096
+// tokens, 127 | 54 at 65536; d 1024, N 32: 264 | 38, 325 | 46, 935 | 525; d 4096, N 61:
+// 965 | 143, 1254 | 183, 3711 | 2159.
 constexpr int kSmallTM = 8;
 constexpr int kSmallKB = 64;
 constexpr int kSmallNC = 64;
-constexpr int kSmallTokens = 4096;
 
 template <typename XT>
 __device__ void project_small(const ProjArgs& a, int64_t t0, float* xs, float* ws,
@@ -1358,9 +1359,7 @@ size_t router_smem(const ProjArgs& a) {
                             (size_t)a.TM * a.NC);
 }
 
-bool vector_small(const pr2_moe_desc& d, int NC) {
-    return NC <= kSmallNC && d.T <= kSmallTokens;
-}
+bool vector_small(int NC) { return NC <= kSmallNC; }
 
 int ncp_of(int NC) { return ((NC + 63) / 64) * 64; }
 
@@ -1511,7 +1510,7 @@ hipError_t launch_route_predict(const pr2_moe_desc& d, const void* x, const floa
     size_t smem = router_smem(a);
     LaunchScope scope("route_predict", s);
     const dim3 small((unsigned)((d.T + kSmallTM - 1) / kSmallTM));
-    if (vector_small(d, NC)) {
+    if (vector_small(NC)) {
         if (d.act_dtype == PR2_BF16)
             hipLaunchKernelGGL((route_predict_kernel<bf16_t, 1, true>), small, dim3(kThreads), 0, s, a, o);
         else
@@ -1567,7 +1566,7 @@ hipError_t launch_router_replay(const pr2_moe_desc& d, const void* x, const floa
     size_t smem = router_smem(a);
     LaunchScope scope(name, s);
     const dim3 small((unsigned)((d.T + kSmallTM - 1) / kSmallTM));
-    if (vector_small(d, d.N)) {
+    if (vector_small(d.N)) {
         if (d.act_dtype == PR2_BF16)
             hipLaunchKernelGGL((replay_gates_kernel<bf16_t, 1, true>), small, dim3(kThreads), 0, s, a, o);
         else

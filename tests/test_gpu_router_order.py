@@ -18,7 +18,7 @@ CASES = [
     (64, 8, 0, "f32"), (64, 8, 4, "f32"), (61, 5, 2, "f32"), (132, 32, 1, "f32"), (260, 61, 3, "f32"),
     (128, 64, 0, "f32"), (68, 64, 8, "f32"), (100, 33, 0, "bf16"), (76, 48, 16, "bf16"),
 ]
-SIZES = (1, 7, 40, 4096, 4097)
+SIZES = (1, 7, 40, 4097, 9000)
 
 
 def problem(d, N, r, act, T):
