@@ -103,22 +103,6 @@ __device__ __forceinline__ uint32_t pack_bf(float lo, float hi) {
     return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
 }
 
-// SwiGLU backward of one element.  H is taken at the precision the forward
-// stores it (rounded to bf16 when round_h), so that dg = <H, G> is the
-// gradient of the computed output.
-__device__ __forceinline__ void swiglu_bwd(float a, float u, float G, float g, bool round_h,
-                                           float& da, float& du, float& hg, float& hG) {
-    const float sig = __builtin_amdgcn_rcpf(1.0f + __expf(-a));   // as the forward's silu
-    const float s = a * sig;
-    float H = s * u;
-    if (round_h) H = bf16_to_f32(f32_to_bf16(H));
-    const float dH = g * G;
-    du = dH * s;
-    da = dH * u * (sig * (1.0f + a * (1.0f - sig)));
-    hg = g * H;
-    hG = H * G;
-}
-
 // all-zero source row for the copies of K rows past an expert's last route
 __device__ __attribute__((aligned(16))) const bf16_t kZeroRow[BN] = {};
 
@@ -426,7 +410,7 @@ bwd_gemm(BwdArgs g) {
                     const float a = h ? bf_hi(av[p][e2]) : bf_lo(av[p][e2]);
                     const float u = h ? bf_hi(uv[p][e2]) : bf_lo(uv[p][e2]);
                     float hG;
-                    swiglu_bwd(a, u, Gv[2 * e2 + h], gq, true, da[h], du[h], hgv[h], hG);
+                    swiglu_bwd<true>(a, u, Gv[2 * e2 + h], gq, da[h], du[h], hgv[h], hG);
                     part += hG;
                 }
                 dw[e2] = pack_bf(da[0], da[1]);

@@ -42,6 +42,23 @@ __device__ __forceinline__ int load_id(const void* idx, int idx_dtype, int64_t p
     return idx_dtype == PR2_I16 ? (int)((const int16_t*)idx)[pos] : ((const int32_t*)idx)[pos];
 }
 
+// SwiGLU backward of one element.  H is taken at the precision the forward
+// stores it (rounded to bf16 when ROUND_H), so that dg = <H, G> is the gradient of
+// the computed output.
+template <bool ROUND_H>
+__device__ __forceinline__ void swiglu_bwd(float a, float u, float G, float g, float& da, float& du,
+                                           float& hg, float& hG) {
+    const float sig = __builtin_amdgcn_rcpf(1.0f + __expf(-a));   // as the MFMA forward's silu
+    const float s = a * sig;
+    float H = s * u;
+    if (ROUND_H) H = bf16_to_f32(f32_to_bf16(H));
+    const float dH = g * G;
+    du = dH * s;
+    da = dH * u * (sig * (1.0f + a * (1.0f - sig)));
+    hg = g * H;
+    hG = H * G;
+}
+
 // ----------------------------------------------------- copies into LDS ----
 typedef __attribute__((address_space(3))) void lds_void;
 

@@ -69,20 +69,6 @@ __device__ __forceinline__ f4 load4(const T* p, int i, int n, bool vec) {
     return r;
 }
 
-// the SwiGLU backward of one element (H at the precision the forward stores it)
-__device__ __forceinline__ void swiglu_grad(float a, float u, float G, float g, bool round_h,
-                                            float& da, float& du, float& hg, float& hG) {
-    const float sig = __builtin_amdgcn_rcpf(1.0f + __expf(-a));
-    const float s = a * sig;
-    float H = s * u;
-    if (round_h) H = bf16_to_f32(f32_to_bf16(H));
-    const float dH = g * G;
-    du = dH * s;
-    da = dH * u * (sig * (1.0f + a * (1.0f - sig)));
-    hg = g * H;
-    hG = H * G;
-}
-
 template <int MODE, typename T>
 __global__ void __launch_bounds__(256) tile_gemm(TileArgs g) {
     constexpr bool kWeight = MODE == T_WD || MODE == T_WGU;     // contracted over routes
@@ -252,8 +238,8 @@ __global__ void __launch_bounds__(256) tile_gemm(TileArgs g) {
                 const T* ain = (const T*)g.AUin + q * 2 * m;
                 T* au = (T*)g.AU + q * 2 * m;
                 float da, du, hg, hG;
-                swiglu_grad(Act<T>::to_f32(ain[c]), Act<T>::to_f32(ain[m + c]), s, gq,
-                            sizeof(T) == 2, da, du, hg, hG);
+                swiglu_bwd<sizeof(T) == 2>(Act<T>::to_f32(ain[c]), Act<T>::to_f32(ain[m + c]), s, gq, da,
+                                           du, hg, hG);
                 au[c] = Act<T>::from_f32(da);
                 au[m + c] = Act<T>::from_f32(du);
                 ((T*)g.H)[q * m + c] = Act<T>::from_f32(hg);
