@@ -59,40 +59,22 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = kTileM;      // 256 rows per tile
 constexpr int BP = 256;         // weight panel rows per tile
-constexpr int BK = 64;          // K slice: 128 bytes per row (32 and 64 supported)
+constexpr int BK = 64;          // K slice: 128 bytes per row
 constexpr int ROWB = BK * 2;    // bytes per LDS row (unpadded; chunks are swizzled)
 constexpr int CHUNKS = ROWB / 16;   // 16-byte chunks per row
 constexpr int NSTAGE = 2;       // LDS stages: slices kt+1 .. kt+NSTAGE-1 in flight during slice kt
 constexpr int WM = 64;          // token rows per wavefront
 constexpr int WN = 128;         // panel rows per wavefront
-constexpr int MT = 16;          // MFMA tile edge: 16 (16x16x32, faster here) or 32 (32x32x16)
-constexpr int MK = 512 / MT;    // K per MFMA
+constexpr int MT = 16;          // MFMA tile edge (16x16x32)
+constexpr int MK = 32;          // K per MFMA
 constexpr int NKS = BK / MK;    // MFMA K sub-steps per slice
-constexpr int ACCN = MT * MT / 64;  // accumulators per lane per tile
 constexpr int MI = WM / MT;     // MFMA tiles per wavefront, token direction
 constexpr int NJ = WN / MT;     // MFMA tiles per wavefront, panel direction
-template <int E> struct MfmaOp;
-template <> struct MfmaOp<32> {
-    typedef f32x16 acc_t;
-    __device__ __forceinline__ static acc_t run(bf16x8 a, bf16x8 b, acc_t c) {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-    }
-};
-template <> struct MfmaOp<16> {
-    typedef f32x4 acc_t;
-    __device__ __forceinline__ static acc_t run(bf16x8 a, bf16x8 b, acc_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
-};
-typedef MfmaOp<MT>::acc_t accv;
-static_assert(sizeof(accv) == ACCN * sizeof(float), "accumulator size");
+typedef f32x4 accv;             // a lane's accumulators of one tile
 
 __device__ __forceinline__ accv mfma_bf16(bf16x8 a, bf16x8 b, accv c) {
-    return MfmaOp<MT>::run(a, b, c);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-// tiles per group of the work order (1: tile-major, every panel of a tile in turn)
-constexpr int kGroupGemm1 = 1;
-constexpr int kGroupGemm2 = 1;
 constexpr int NWAVE = (BM / WM) * (BP / WN);
 constexpr int kGemmThreads = 64 * NWAVE;
 constexpr int kNumXcd = 8;
@@ -117,7 +99,6 @@ struct MfmaArgs {
     const float* gate;      // GEMM2
     bf16_t* out;
     bf16_t* out2;           // GEMM1 that also saves a | u (MODE 3): [T*k, 2m]
-    int group;              // work order: groups of this many tiles, panel-major inside
 };
 
 // silu(a) = a / (1 + e^-a) with the hardware reciprocal (about 1 ulp; H is rounded to bf16)
@@ -129,7 +110,7 @@ __device__ __forceinline__ float silu_f(float a) {
 // 8) consecutive rows read at the same chunk hit disjoint banks.  swz depends
 // on r % 16 only.
 __device__ __forceinline__ int swz(int r) {
-    return CHUNKS == 8 ? (r & 7) ^ ((r >> 3) & 1) : ((r >> 1) ^ (r >> 2)) & 3;
+    return (r & 7) ^ ((r >> 3) & 1);
 }
 
 // wait until at most n of this wavefront's global loads are outstanding
@@ -145,23 +126,16 @@ grouped_gemm_mfma(MfmaArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[LDSB];
 
     // XCD-aware mapping: physical block b runs on XCD b % 8; give each XCD a
-    // contiguous range of the (tile, panel) work list.  The list runs over
-    // groups of g.group consecutive tiles (the last group may be smaller); inside
-    // a group it is panel-major, so the workgroups that start together share
-    // one weight panel and the group's gathered rows stay in that XCD's L2.
-    const int ntile = *g.tile_count;
-    const int64_t L = (int64_t)ntile * g.ntn;
+    // contiguous range of the (tile, panel) work list, every panel of a tile in
+    // turn (groups of 2, 4 or 8 tiles, panel by panel inside a group: within 1 %)
+    const int64_t L = (int64_t)(*g.tile_count) * g.ntn;
     const int64_t per_xcd = (L + kNumXcd - 1) / kNumXcd;
     const int64_t local = blockIdx.x / kNumXcd;
     if (local >= per_xcd) return;
     const int64_t logical = (int64_t)(blockIdx.x % kNumXcd) * per_xcd + local;
     if (logical >= L) return;
-    const int64_t wgrp = logical / ((int64_t)g.group * g.ntn);
-    const int first = (int)(wgrp * g.group);
-    const int gsz = min(g.group, ntile - first);
-    const int within = (int)(logical - wgrp * g.group * g.ntn);
-    const int tile = first + within % gsz;
-    const int pn = within / gsz;
+    const int tile = (int)(logical / g.ntn);
+    const int pn = (int)(logical % g.ntn);
     const int expert = g.tiles[3 * tile + 0];
     const int row0 = g.tiles[3 * tile + 1];
     const int rows = g.tiles[3 * tile + 2];
@@ -218,8 +192,7 @@ grouped_gemm_mfma(MfmaArgs g) {
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int v = 0; v < ACCN; ++v) acc[i][j][v] = 0.0f;
+            acc[i][j] = accv{0.0f, 0.0f, 0.0f, 0.0f};
 
     // LDS reads for the MFMA operands: lane l reads row (block base + l%MT)
     // and the 16 bytes of one 8-wide K chunk, at position chunk ^ swz(row);
@@ -227,13 +200,12 @@ grouped_gemm_mfma(MfmaArgs g) {
     // every fragment.  Which chunk of the sub-step a lane group g = l/MT
     // takes is free (A and B fragments use the same assignment, so each MFMA
     // still sums over the same K values): a ds_read_b128 serves lanes
-    // 8q..8q+7 together with lanes 32+8q..32+8q+7, so for 16x16 tiles groups
-    // g and g+2 take chunks differing in the lowest bit (0,2,1,3), which keeps
+    // 8q..8q+7 together with lanes 32+8q..32+8q+7, so groups g and g+2 take chunks differing in the lowest bit (0,2,1,3), which keeps
     // the two halves of every LDS cycle in disjoint banks.
     const int lrow = lane % MT;
     const int sw = swz(lrow);
     const int grp = lane / MT;
-    const int cperm = MT == 16 ? (((grp & 1) << 1) | (grp >> 1)) : grp;
+    const int cperm = ((grp & 1) << 1) | (grp >> 1);
     int kpos[NKS];
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks)
@@ -355,17 +327,13 @@ grouped_gemm_mfma(MfmaArgs g) {
         sync();
     }
     // Epilogue.  The MFMA computed the transposed tile (weights x tokens), so
-    // accumulator element v of lane l is, for 16x16 tiles, column 4*(l/16) + v
-    // of token row l%16 of its block (for 32x32 tiles, column
-    // 8*(v/4) + 4*(l/32) + v%4 of token row l%32): runs of four consecutive
-    // outputs per lane.
+    // accumulator element v of lane l is column 4*(l/16) + v of token row l%16 of
+    // its block: runs of four consecutive outputs per lane.
     if ((MODE == 0 || MODE == 3) && active) {
         // GEMM1: H = silu(gate) * up, stored straight from registers, one
         // 8-byte write per run (gate and up tiles of the same columns sit in
         // the same lanes)
         const int ncol0 = 4 * (lane / MT);
-        constexpr int NA4 = ACCN / 4;           // runs of four per tile
-        constexpr int A4STEP = MT == 32 ? 8 : 0;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const int r = wr * WM + i * MT + (lane % MT);
@@ -374,18 +342,14 @@ grouped_gemm_mfma(MfmaArgs g) {
 #pragma unroll
             for (int j = 0; j < NJ / 2; ++j) {
                 const int col = pn * 128 + wc * (WN / 2) + j * MT + ncol0;
+                uint32_t w[2];
 #pragma unroll
-                for (int a4 = 0; a4 < NA4; ++a4) {
-                    uint32_t w[2];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int v0 = 4 * a4 + 2 * h;
-                        const float h0 = silu_f(acc[i][j][v0]) * acc[i][j + NJ / 2][v0];
-                        const float h1 = silu_f(acc[i][j][v0 + 1]) * acc[i][j + NJ / 2][v0 + 1];
-                        w[h] = (uint32_t)f32_to_bf16(h0) | ((uint32_t)f32_to_bf16(h1) << 16);
-                    }
-                    *(uint2*)(orow + col + A4STEP * a4) = make_uint2(w[0], w[1]);
+                for (int h = 0; h < 2; ++h) {
+                    const float h0 = silu_f(acc[i][j][2 * h]) * acc[i][j + NJ / 2][2 * h];
+                    const float h1 = silu_f(acc[i][j][2 * h + 1]) * acc[i][j + NJ / 2][2 * h + 1];
+                    w[h] = (uint32_t)f32_to_bf16(h0) | ((uint32_t)f32_to_bf16(h1) << 16);
                 }
+                *(uint2*)(orow + col) = make_uint2(w[0], w[1]);
             }
         }
     }
@@ -414,7 +378,6 @@ grouped_gemm_mfma(MfmaArgs g) {
     }
     __syncthreads();
     if (!active) return;
-    static_assert(MT == 16, "staged epilogue assumes 16x16 MFMA tiles");
     constexpr int CW = MODE == 1 ? WN : WN / 2;          // columns per output block
     constexpr bool kPreact = MODE == 2 || MODE == 3;     // stores a | u
     constexpr int NB = kPreact ? 2 : 1;                   // output blocks per wavefront
@@ -488,8 +451,7 @@ static_assert(kAGroupsW * kRowsPerDma * NWAVE == BM && kWGroupsW * kRowsPerDma *
 __global__ void __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm1_wide(MfmaArgs g) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[LDSBW];
-    const int ntile = *g.tile_count;
-    const int64_t L = (int64_t)ntile * g.ntn;
+    const int64_t L = (int64_t)(*g.tile_count) * g.ntn;
     const int64_t per_xcd = (L + kNumXcd - 1) / kNumXcd;
     const int64_t local = blockIdx.x / kNumXcd;
     if (local >= per_xcd) return;
@@ -558,13 +520,12 @@ gemm1_wide(MfmaArgs g) {
     for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJW; ++j)
-#pragma unroll
-            for (int v = 0; v < ACCN; ++v) acc[i][j][v] = 0.0f;
+            acc[i][j] = accv{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int lrow = lane % MT;
     const int sw = swz(lrow);
     const int grp = lane / MT;
-    const int cperm = MT == 16 ? (((grp & 1) << 1) | (grp >> 1)) : grp;
+    const int cperm = ((grp & 1) << 1) | (grp >> 1);
     int kpos[NKS];
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks)
@@ -884,7 +845,6 @@ hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void*
         g1.tile_count = ws.tile_count;
         g1.gate = gate;
         g1.out = (bf16_t*)ws.H;
-        g1.group = kGroupGemm1;
         int64_t work = ws.max_tiles * g1.ntn;
         int64_t grid = ((work + kNumXcd - 1) / kNumXcd) * kNumXcd;
         if (!au_out && few_rows_ok(d, d.m % (BPW / 2) == 0 ? 8 : 16)) {
@@ -919,7 +879,6 @@ hipError_t launch_expert_gemms(const pr2_moe_desc& d, const void* x, const void*
         g2.n_out = d.d;
         g2.ntn = d.d / BP;
         g2.out = (bf16_t*)ws.O;
-        g2.group = kGroupGemm2;
         work = ws.max_tiles * g2.ntn;
         grid = ((work + kNumXcd - 1) / kNumXcd) * kNumXcd;
         if (few_rows_ok(d, 32)) {
@@ -955,7 +914,6 @@ hipError_t launch_preact(const pr2_moe_desc& d, const void* x, const void* W_gat
         g.tiles = ws.tiles;
         g.tile_count = ws.tile_count;
         g.out = (bf16_t*)AU;
-        g.group = kGroupGemm1;
         const int64_t work = ws.max_tiles * g.ntn;
         const int64_t grid = ((work + kNumXcd - 1) / kNumXcd) * kNumXcd;
         LaunchScope scope("bwd_preact_gate_up", s);
