@@ -1231,7 +1231,7 @@ literal_dx_combine_kernel(const T* dxr, const int* inv, const float* dpf, const 
 }
 
 // The same with four consecutive columns per thread (d % 4 == 0): each
-// broadcast LDS read of four logits feeds 64 FMAs; every output's sums run in
+// broadcast LDS read of four logits feeds 16 FMAs; every output's sums run in
 // the same order as above, so the result is bitwise the same.  Four tokens per
 // workgroup: bound by the latency of the W_r and route-row loads, so many short
 // workgroups beat fewer that share each W_r row (16, 8, 4 tokens at d 2048: 72,

@@ -67,8 +67,11 @@ typedef __attribute__((address_space(3))) void lds_void;
 // issued through the compiler builtin, every later LDS read that carries no
 // type-based alias information (the transposing reads do not) is made to wait
 // for all copies in flight, which serialises each K slice's copies with the
-// slice before.  The K loop waits for its own copies explicitly (vmcnt 0 ahead
-// of the barrier that publishes a stage), so nothing relies on that wait.
+// slice before.  Nothing relies on that wait: in every K loop each wavefront
+// waits, ahead of the barrier that publishes a stage, until its own copies into that
+// stage have landed.  Two-stage loops wait for all copies (vmcnt 0); loops over a
+// ring of stages (few rows, backward, weight gradients) for a count, the copies it
+// has issued since for the stages after, so that count has to match what it issues.
 // M0 takes the LDS base; the nop covers the M0-write -> LDS-DMA hazard.  The
 // compiler keeps no value of its own in M0 in these kernels (it sets M0 only
 // right before its own LDS-DMA and message instructions, and they use none),

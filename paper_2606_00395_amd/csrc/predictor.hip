@@ -9,11 +9,12 @@
 //   dB = sum_t u_t^T dz_t,  dA = sum_t h_old,t^T (dz_t B^T)
 //
 // p comes from the replay router kernels (exact products, one rounding to fp32).
-// Everything after it runs in fp64.  The three products u = h_old A,
-// dB = u^T dz and dA = h_old^T w go through one tiled kernel: a workgroup forms
-// a 64 x 16 output tile over one slice of the summed index, staging both
-// operands through LDS as fp64, and a second kernel adds the slices in slice
-// order.  The two softmaxes, the KL and dz take one wavefront per token.  The
+// Everything after it runs in fp64.  bf16 features of the models' shapes take
+// three launches (pred_token, pred_grad, pred_finish; below).  Elsewhere the three
+// products u = h_old A, dB = u^T dz and dA = h_old^T w go through one tiled kernel:
+// a workgroup forms a 64 x 16 output tile over one slice of the summed index,
+// staging both operands through LDS as fp64, and a second kernel adds the slices in
+// slice order; the two softmaxes, the KL and dz take one wavefront per token.  All
 // sums are deterministic (no atomics).
 #include <algorithm>
 
@@ -155,6 +156,15 @@ hipError_t launch_prod(const TA* a, int64_t a_m, int64_t a_k, const TB* b, int64
 // barriers (2048 tokens, d 2048, N 128, r 16: 73 us in eight launches, 36 in three).
 // u runs on the vector ALU: its fp64 matrix instructions (16x16x4), issued once in
 // about 226 clocks, made the token kernel 27 us instead of 20.
+//
+// Limits: d % 64 is the token kernel's K step (8 values for each of 8 lane groups);
+// the kernel's LDS is sized for r <= 64.  Above 192 columns the logits have no MFMA
+// form and take nearly all of the call (2048 tokens, d 2048, N 256, r 16: 1341 us in
+// eight launches, 1290 with this path), so it ends where that form ends.  Calls in
+// eight launches | in three, us: d 2048, N 128, r 16 51 | 33 at 1 token, 73 | 49 at
+// 512, 104 | 60 at 2048, 807 | 464 at 32768; d 2048, N 128, r 1 55 | 43 at 512; d
+// 4096, N 128, r 64 112 | 107 at 64, 362 | 206 at 2048; d 1024, N 192, r 32 73 | 40
+// at 1, 1026 | 543 at 32768.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 // four floats of a tensor that is only promised to start at a 4-byte boundary (A); the
@@ -163,8 +173,15 @@ typedef f4 f4_unaligned __attribute__((aligned(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
 constexpr int kPTok = 8;            // tokens per workgroup, one wavefront each
-constexpr int kGradTok = 64;        // fewest tokens per gradient slice
-constexpr int kGradSlices = 64;     // most slices
+// Fewest tokens per slice of the gradient sums, and most slices.  A slice is a serial
+// chain of loads and MFMAs, and its partial sums are written and read once.  Whole call
+// in us with (tokens, slices) of (64, 64) | (32, 64) | (128, 64) | (64, 32) | (64, 128):
+// d 2048, N 128, r 16 43 | 40 | 48 | 43 | 43 at 300 tokens, 60 | 61 | 67 | 60 | 60 at
+// 2048 (a response's feature cache, the usual size), 233 | 233 | 233 | 246 | 223 at 16384;
+// d 4096, N 128, r 64 136 | 136 | 141 | 136 | 136, 206 | 220 | 207 | 206 | 206 and 1213 |
+// 1212 | 1213 | 1196 | 1253 (134 MB of partial sums at 64 slices, and 128 add more).
+constexpr int kGradTok = 64;
+constexpr int kGradSlices = 64;
 
 // value e (0..7) of 8 consecutive bf16
 __device__ __forceinline__ double bf8(u32x4 v, int e) {

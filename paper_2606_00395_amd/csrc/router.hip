@@ -1187,10 +1187,13 @@ router_mfma_kernel(const bf16_t* x, const bf16_t* Ws, int64_t T, int d, int N, i
     float* lg = (float*)lds;
     if (PHASE == 2) {
         // logit (row wave + 8 a, column lane + 64 b): the fp64 sum over the K
-        // pairs, in order, of phase 1's partial sums, rounded once; 32 pairs (d =
-        // 2048: all) of every element are loaded before any is added, the rest
-        // eight at a time (eight at a time throughout: 8.4 us for 256 tokens, N
-        // 128, against 7.7).  Rows up to the last tile's end exist.
+        // pairs, in order, of phase 1's partial sums, rounded once; 32 pairs
+        // (2048 of d) of every element are loaded before any is added, the rest
+        // eight at a time.  (Eight throughout: 8.4 us for 256 tokens, d 2048, N
+        // 128, against 7.7; whole step with eight | sixteen | 32 at a time 17.1 |
+        // 16.6 | 16.6 us at 256 tokens, d 4096, 26.2 | 26.1 | 25.7 at 2048 tokens, d
+        // 2048, the same at 1000 and 2048 tokens with d above 2048.  Below d 2048
+        // only the eights run.)  Rows up to the last tile's end exist.
         static_assert(TOK % (kRThreads / 64) == 0, "rows per wavefront");
         constexpr int RPW = TOK / (kRThreads / 64);
         const int64_t pstride = sk.rows * NCp;
