@@ -452,8 +452,8 @@ bwd_gemm(BwdArgs g) {
 // holds the step's last fragments then, so its stage takes the copies of step
 // h + 4 and the fragments of step h + 1 are read among the MFMAs.
 // The gathered operand's row offsets are put into LDS once per tile (8192 routes
-// at a time); K rows past the last route read zeros in the plain operand and the
-// expert's last route in the gathered one.
+// at a time); K rows past the last route are zeros in both operands (a row of the
+// gathered one, times zero, would turn an infinity of its own gradient into a NaN).
 constexpr int kWgRoutes = 8192;                    // route offsets held in LDS
 
 template <int MODE>
@@ -544,9 +544,18 @@ bwd_wgrad(BwdArgs g) {
         };
         auto issue_gathered = [&](int h) __attribute__((always_inline)) {
             unsigned char* dst = lds + (h % kStages) * kStageB + half * kOpB + wq * 4096;
+            const int k0 = h * kBK + 8 * wq;
+            if ((h + 1) * kBK <= clen) {
 #pragma unroll
-            for (int i = 0; i < kCopies; ++i)
-                dma16_at(gbase, go[i] + 2u * (uint32_t)cpat[i & 1], dst + i * 1024);
+                for (int i = 0; i < kCopies; ++i)
+                    dma16_at(gbase, go[i] + 2u * (uint32_t)cpat[i & 1], dst + i * 1024);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kCopies; ++i)
+                    dma16(k0 + 2 * i + hi < clen ? (const unsigned char*)(gbase + cpat[i & 1]) + go[i]
+                                                 : (const unsigned char*)(kZeroRow + cpat[i & 1]),
+                          dst + i * 1024);
+            }
         };
         auto issue_plain = [&](int h) __attribute__((always_inline)) {
             unsigned char* dst = lds + (h % kStages) * kStageB + half * kOpB + wq * 4096;
